@@ -559,6 +559,8 @@ cobs_status_t cobs_compression_branch(const cobs_config_t* cfg, const float* q, 
   p.tmax = v.tmax;
   p.mdt = v.mdt;
   p.lsh = v.lsh;
+  p.units = 0;
+  p.nsplit = 0;
   p.c = v.c;
   p.lay = v.lay;
   return hip_status(launch_compress(p, v.d, v.G, v.B, static_cast<hipStream_t>(stream)));

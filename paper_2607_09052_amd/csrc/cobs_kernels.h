@@ -82,10 +82,11 @@ struct CompressParams {
   float* out;
   float* lse;
   int hkv, hq, nbmax, tmax, mdt, lsh;
+  int units, nsplit;    // B*Hkv; workgroups a unit's query heads are split over (set by the launcher)
   float c;
   RecLayout lay;
 };
-hipError_t launch_compress(const CompressParams& p, int d, int g, int batch, hipStream_t st);
+hipError_t launch_compress(CompressParams p, int d, int g, int batch, hipStream_t st);
 hipError_t launch_pack_e2m1(const float* x, int64_t nvec, int dim, uint8_t* codes, float* scales,
                             hipStream_t st);
 // Launchers choose the grid (chunks / work items per workgroup) from the

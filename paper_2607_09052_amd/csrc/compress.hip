@@ -3,191 +3,176 @@
 // blocks, block b entering as one key (its stored mean key) with one value (its
 // stored mean value), over every block b < ceil(T/L).
 //
-// One 256-thread workgroup per (batch row, KV head).  Wave w takes blocks
-// w*64 + lane, + 256, ...: in the score pass lane l reads block l's mean key
-// from its record and forms its G scores against the queries in LDS; the
-// streaming softmax statistics per head are wave reductions; the probabilities
-// go through LDS to the value pass, where lane l holds output elements
-// [l D/64, (l+1) D/64) and reads them from each block's mean value (one
-// coalesced run per block).  The four waves' states merge in LDS and the
-// workgroup writes out and lse.  The records are read once.
+// A workgroup of 16 waves takes HW query heads of one (batch row, KV head).
+// Sixteen lanes share a block: lane ln owns elements [ln D/16, (ln+1) D/16) of
+// its mean key and mean value, so a load instruction reads four whole vectors,
+// the scores are 16-lane DPP sums that every lane of the group ends with, and
+// the probabilities meet the values in the same lanes, with no LDS in the loop.
+// A group takes four blocks at a time (all of their loads in flight, one rescale
+// of its running state per head); the 64 groups' states merge in lane,
+// then wave order.
+//
+// What bounds it: latency (the bytes of a case here, 17 MB for 4 x 8 units of
+// 1024 blocks, are 3.5 us at the copy rate) and, with all heads of a large
+// group in one workgroup, its CU's vector ALUs (2 G D multiply-adds per block).
+// So the heads are split over workgroups until the chip is covered (see
+// launch_compress); the workgroups of one unit read the same records, the
+// later ones from L2.  10.7 us a call at that case (4 heads per KV head, bf16
+// means; one 256-thread workgroup per unit, whose value pass loaded one block
+// at a time, took 47.4).
 #include "select_impl.h"
 
 namespace cobs {
 
-constexpr int kCmpThreads = 256;
+constexpr int kCmpThreads = 1024;
 
-// The mean key of one record as D floats, dequantized (E2M1 with its scale).
-template <int D, int MDT>
-__device__ __forceinline__ void load_mean_key(const uint8_t* R, const RecLayout& lay, float* x) {
-  const uint8_t* m = R + lay.mean_off;
-  if constexpr (MDT == DT_F32) {
-#pragma unroll
-    for (int e = 0; e < D; e += 4) {
-      const float4 v = *reinterpret_cast<const float4*>(m + 4 * e);
-      x[e] = v.x; x[e + 1] = v.y; x[e + 2] = v.z; x[e + 3] = v.w;
-    }
-  } else if constexpr (MDT == DT_BF16) {
-#pragma unroll
-    for (int e = 0; e < D; e += 8) {
-      const uint4 v = *reinterpret_cast<const uint4*>(m + 2 * e);
-      x[e] = bf16_lo(v.x); x[e + 1] = bf16_hi(v.x); x[e + 2] = bf16_lo(v.y); x[e + 3] = bf16_hi(v.y);
-      x[e + 4] = bf16_lo(v.z); x[e + 5] = bf16_hi(v.z); x[e + 6] = bf16_lo(v.w); x[e + 7] = bf16_hi(v.w);
-    }
-  } else {
-    const float sc = *reinterpret_cast<const float*>(R + 4);
-#pragma unroll
-    for (int e = 0; e < D; e += 32) {
-      const uint4 v = *reinterpret_cast<const uint4*>(m + e / 2);
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        // byte j of the word holds elements 2j (low nibble) and 2j + 1
-        const auto f0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[k], 1.0f, 0);
-        const auto f1 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[k], 1.0f, 1);
-        const auto f2 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[k], 1.0f, 2);
-        const auto f3 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[k], 1.0f, 3);
-        float* y = x + e + 8 * k;
-        y[0] = f0[0] * sc; y[1] = f0[1] * sc; y[2] = f1[0] * sc; y[3] = f1[1] * sc;
-        y[4] = f2[0] * sc; y[5] = f2[1] * sc; y[6] = f3[0] * sc; y[7] = f3[1] * sc;
-      }
-    }
-  }
+// Blocks of a 16-lane group per pass: two where four would spill (128 registers).
+template <int D, int HW, int MDT>
+constexpr int cmp_batch() { return (D == 128 && HW == 4 && MDT != DT_BF16) ? 2 : 4; }
+
+// Elements [ln D/16, (ln+1) D/16) of a stored vector as raw words (E2M1 at
+// D = 64: four codes, the low half word).
+template <int D, int DT>
+__device__ __forceinline__ void load_part(const uint8_t* vec, int ln, uint32_t* w) {
+  constexpr int B = elem_bytes<DT>(D / 16);
+  if constexpr (B >= 4) load_words<B / 4>(vec + ln * B, w);
+  else w[0] = *reinterpret_cast<const uint16_t*>(vec + ln * B);
 }
 
-// Elements [l EPL, (l+1) EPL) of one record's mean value (EPL = D / 64).
-template <int D, int MDT>
-__device__ __forceinline__ void load_value_slice(const uint8_t* R, const RecLayout& lay, int l, float* x) {
-  constexpr int EPL = D / 64;
-  const uint8_t* m = R + lay.vmean_off;
-  if constexpr (MDT == DT_F32) {
-    if constexpr (EPL == 2) {
-      const float2 v = reinterpret_cast<const float2*>(m)[l];
-      x[0] = v.x; x[1] = v.y;
-    } else {
-      x[0] = reinterpret_cast<const float*>(m)[l];
-    }
-  } else if constexpr (MDT == DT_BF16) {
-    if constexpr (EPL == 2) {
-      const uint32_t v = reinterpret_cast<const uint32_t*>(m)[l];
-      x[0] = bf16_lo(v); x[1] = bf16_hi(v);
-    } else {
-      x[0] = __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(m)[l] << 16);
-    }
-  } else {
-    const float sc = *reinterpret_cast<const float*>(R + 8);
-    if constexpr (EPL == 2) {
-      const uint32_t byte = m[l];
-      x[0] = e2m1_value(byte & 15u) * sc;
-      x[1] = e2m1_value(byte >> 4) * sc;
-    } else {
-      const uint32_t byte = m[l >> 1];
-      x[0] = e2m1_value((l & 1) ? (byte >> 4) : (byte & 15u)) * sc;
-    }
-  }
-}
+template <int D, int DT>
+constexpr int part_words() { return elem_bytes<DT>(D / 16) >= 4 ? elem_bytes<DT>(D / 16) / 4 : 1; }
 
-template <int D, int G, int MDT>
+template <int D, int HW, int MDT>
 __global__ __launch_bounds__(kCmpThreads) void compress_kernel(CompressParams p) {
-  constexpr int EPL = D / 64;
-  constexpr int GP = (G + 3) / 4 * 4;
-  __shared__ __align__(16) float qs[G][D];
-  __shared__ __align__(16) float ps[4][64][GP];
-  __shared__ float wm[4][G], wl[4][G];
-  __shared__ float wo[4][G][D];
+  constexpr int EPL = D / 16, NW = kCmpThreads / 64, U = cmp_batch<D, HW, MDT>();
+  constexpr int MW = part_words<D, MDT>();
+  __shared__ float wm[NW][HW], wl[NW][HW];
+  __shared__ __align__(16) float wo[NW][HW][D];
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int unit = blockIdx.x;
+  const int ln = lane & 15, grp = lane >> 4;
+  // workgroups in runs of 8 units: the head splits of a unit are 8 indices
+  // apart, on one XCD (its L2 serves all but the first) and dispatched together
+  const int nsp = p.nsplit, run = 8 * nsp;
+  const int unit = (int)(blockIdx.x / run) * 8 + (int)(blockIdx.x % 8), split = (int)(blockIdx.x % run) / 8;
+  if (unit >= p.units) return;
   const int b = unit / p.hkv, h = unit % p.hkv;
-  const int T = clamp_len(p.seq_lens[b], p.tmax);
-  const int nb = blocks_of(T, p.lsh);
+  const int nb = blocks_of(clamp_len(p.seq_lens[b], p.tmax), p.lsh);
   const uint8_t* recu = p.rec + (int64_t)unit * p.nbmax * p.lay.total;
-  for (int idx = tid; idx < G * D; idx += kCmpThreads)
-    qs[idx / D][idx % D] = p.q[((int64_t)b * p.hq + h * G) * D + idx] * p.c;
-  __syncthreads();
+  const int64_t head0 = (int64_t)b * p.hq + (int64_t)h * (HW * nsp) + split * HW;
 
-  float m[G], l[G], o[G][EPL];
+  float q[HW][EPL], m[HW], l[HW], o[HW][EPL];
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
+  for (int g = 0; g < HW; ++g) {
     m[g] = -INFINITY;
     l[g] = 0.0f;
 #pragma unroll
+    for (int e = 0; e < EPL; e += 4) {
+      const float4 x = *reinterpret_cast<const float4*>(p.q + (head0 + g) * D + EPL * ln + e);
+      q[g][e] = x.x * p.c; q[g][e + 1] = x.y * p.c; q[g][e + 2] = x.z * p.c; q[g][e + 3] = x.w * p.c;
+    }
+#pragma unroll
     for (int e = 0; e < EPL; ++e) o[g][e] = 0.0f;
   }
-  for (int base = 64 * wave; base < nb; base += kCmpThreads) {
-    // ---- scores: lane = block
-    const int blk = base + lane;
-    const bool live = blk < nb;
-    float sc[G];
+
+  for (int base = 4 * U * wave; base < nb; base += 4 * U * NW) {
+    // block base + 4 u + grp of pass element u; past the last block its record
+    // is read again and its score is -inf
+    uint32_t kw[U][MW], vw[U][MW];
+    float ks[U], vs[U];
 #pragma unroll
-    for (int g = 0; g < G; ++g) sc[g] = 0.0f;
-    {
-      float x[D];
-      load_mean_key<D, MDT>(recu + (int64_t)(live ? blk : base) * p.lay.total, p.lay, x);
+    for (int u = 0; u < U; ++u) {
+      const uint8_t* R = recu + (int64_t)min(base + 4 * u + grp, nb - 1) * p.lay.total;
+      load_part<D, MDT>(R + p.lay.mean_off, ln, kw[u]);
+      load_part<D, MDT>(R + p.lay.vmean_off, ln, vw[u]);
+      ks[u] = (MDT == DT_E2M1) ? *reinterpret_cast<const float*>(R + 4) : 1.0f;
+      vs[u] = (MDT == DT_E2M1) ? *reinterpret_cast<const float*>(R + 8) : 1.0f;
+    }
+    float sc[U][HW];
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
+    for (int u = 0; u < U; ++u) {
+      const bool live = base + 4 * u + grp < nb;
+      float x[EPL];
+      unpack_elems<MDT, EPL>(kw[u], x);
+#pragma unroll
+      for (int g = 0; g < HW; ++g) {
         float a = 0.0f;
 #pragma unroll
-        for (int e = 0; e < D; e += 4) {
-          const float4 qq = *reinterpret_cast<const float4*>(&qs[g][e]);
-          a += x[e] * qq.x + x[e + 1] * qq.y + x[e + 2] * qq.z + x[e + 3] * qq.w;
-        }
-        sc[g] = a;
+        for (int e = 0; e < EPL; ++e) a += x[e] * q[g][e];
+        a = row16_sum(a) * ks[u];
+        sc[u][g] = live ? a : -INFINITY;
       }
     }
-    // ---- streaming softmax update per head
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const float sg = live ? sc[g] : -INFINITY;
-      const float mn = fmaxf(m[g], wave_max(sg));
-      const float alpha = (m[g] == -INFINITY) ? 0.0f : __expf(m[g] - mn);
-      const float pr = live ? __expf(sg - mn) : 0.0f;
-      l[g] = l[g] * alpha + wave_sum(pr);
+    for (int g = 0; g < HW; ++g) {
+      float mn = m[g];
+#pragma unroll
+      for (int u = 0; u < U; ++u) mn = fmaxf(mn, sc[u][g]);
+      // (a group whose blocks all lie past the end keeps its empty state)
+      const float ref = (mn == -INFINITY) ? 0.0f : mn;
+      const float alpha = __expf(m[g] - ref);
       m[g] = mn;
-      ps[wave][lane][g] = pr;
+      l[g] *= alpha;
 #pragma unroll
       for (int e = 0; e < EPL; ++e) o[g][e] *= alpha;
-    }
-    wave_lds_sync();
-    // ---- values: lane = output slice, one block at a time
-    const int cnt = min(64, nb - base);
-    for (int j = 0; j < cnt; ++j) {
-      float v[EPL];
-      load_value_slice<D, MDT>(recu + (int64_t)(base + j) * p.lay.total, p.lay, lane, v);
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const float pj = ps[wave][j][g];
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) o[g][e] += pj * v[e];
+      for (int u = 0; u < U; ++u) {
+        sc[u][g] = __expf(sc[u][g] - ref);
+        l[g] += sc[u][g];
       }
     }
-    wave_lds_sync();      // ps is rewritten by the next pass
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float x[EPL];
+      unpack_elems<MDT, EPL>(vw[u], x);
+#pragma unroll
+      for (int g = 0; g < HW; ++g) {
+        const float pr = sc[u][g] * vs[u];
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) o[g][e] += pr * x[e];
+      }
+    }
   }
-  // ---- the four waves' states, merged in wave order
-  if (lane == 0) {
+  // ---- the four groups' states of the wave
 #pragma unroll
-    for (int g = 0; g < G; ++g) { wm[wave][g] = m[g]; wl[wave][g] = l[g]; }
+  for (int k = 16; k < 64; k <<= 1) {
+#pragma unroll
+    for (int g = 0; g < HW; ++g) {
+      const float m2 = __shfl_xor(m[g], k, 64), l2 = __shfl_xor(l[g], k, 64);
+      const float mn = fmaxf(m[g], m2), ref = (mn == -INFINITY) ? 0.0f : mn;
+      const float f1 = __expf(m[g] - ref), f2 = __expf(m2 - ref);
+      m[g] = mn;
+      l[g] = f1 * l[g] + f2 * l2;
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) o[g][e] = f1 * o[g][e] + f2 * __shfl_xor(o[g][e], k, 64);
+    }
   }
+  if (grp == 0) {
 #pragma unroll
-  for (int g = 0; g < G; ++g)
+    for (int g = 0; g < HW; ++g) {
+      if (ln == 0) { wm[wave][g] = m[g]; wl[wave][g] = l[g]; }
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) wo[wave][g][lane * EPL + e] = o[g][e];
+      for (int e = 0; e < EPL; e += 4)
+        *reinterpret_cast<float4*>(&wo[wave][g][EPL * ln + e]) = make_float4(o[g][e], o[g][e + 1], o[g][e + 2], o[g][e + 3]);
+    }
+  }
   __syncthreads();
-  for (int idx = tid; idx < G * D; idx += kCmpThreads) {
+  // ---- the waves' states, merged in wave order
+  for (int idx = tid; idx < HW * D; idx += kCmpThreads) {
     const int g = idx / D, dd = idx % D;
     float M = -INFINITY;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) M = fmaxf(M, wm[k][g]);
+    for (int k = 0; k < NW; ++k) M = fmaxf(M, wm[k][g]);
     float acc = 0.0f, lsum = 0.0f;
     if (M != -INFINITY) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float f = (wm[k][g] == -INFINITY) ? 0.0f : __expf(wm[k][g] - M);
+      for (int k = 0; k < NW; ++k) {
+        const float f = __expf(wm[k][g] - M);
         acc += f * wo[k][g][dd];
         lsum += f * wl[k][g];
       }
     }
-    const int64_t oq = (int64_t)b * p.hq + h * G + g;
+    const int64_t oq = head0 + g;
     p.out[oq * D + dd] = (lsum > 0.0f) ? acc / lsum : 0.0f;
     if (dd == 0 && p.lse) p.lse[oq] = (lsum > 0.0f) ? M + logf(lsum) : -INFINITY;
   }
@@ -196,26 +181,33 @@ __global__ __launch_bounds__(kCmpThreads) void compress_kernel(CompressParams p)
 typedef void (*CompressKernel)(CompressParams);
 
 template <int D, int MDT>
-static CompressKernel compress_kernel_g(int g) {
-  switch (g) {
+static CompressKernel compress_kernel_h(int hw) {
+  switch (hw) {
     case 1: return compress_kernel<D, 1, MDT>;
     case 2: return compress_kernel<D, 2, MDT>;
-    case 4: return compress_kernel<D, 4, MDT>;
-    case 8: return compress_kernel<D, 8, MDT>;
-    default: return compress_kernel<D, 16, MDT>;
+    default: return compress_kernel<D, 4, MDT>;
   }
 }
 
 template <int D>
-static CompressKernel compress_kernel_m(int mdt, int g) {
-  if (mdt == DT_F32) return compress_kernel_g<D, DT_F32>(g);
-  if (mdt == DT_BF16) return compress_kernel_g<D, DT_BF16>(g);
-  return compress_kernel_g<D, DT_E2M1>(g);
+static CompressKernel compress_kernel_m(int mdt, int hw) {
+  if (mdt == DT_F32) return compress_kernel_h<D, DT_F32>(hw);
+  if (mdt == DT_BF16) return compress_kernel_h<D, DT_BF16>(hw);
+  return compress_kernel_h<D, DT_E2M1>(hw);
 }
 
-hipError_t launch_compress(const CompressParams& p, int d, int g, int batch, hipStream_t st) {
-  const CompressKernel k = (d == 128) ? compress_kernel_m<128>(p.mdt, g) : compress_kernel_m<64>(p.mdt, g);
-  hipLaunchKernelGGL(k, dim3((unsigned)(batch * p.hkv)), dim3(kCmpThreads), 0, st, p);
+// Heads per workgroup: at most 4 (the queries and running outputs of more do
+// not fit the 128 registers that 16 waves leave a lane), halved while the
+// units alone leave CUs idle.
+hipError_t launch_compress(CompressParams p, int d, int g, int batch, hipStream_t st) {
+  const int64_t units = (int64_t)batch * p.hkv;
+  int hw = std::min(g, 4);
+  while (hw > 1 && units * (g / hw) < device_cus()) hw /= 2;
+  p.units = (int)units;
+  p.nsplit = g / hw;
+  const CompressKernel k = (d == 128) ? compress_kernel_m<128>(p.mdt, hw) : compress_kernel_m<64>(p.mdt, hw);
+  const int64_t grid = (units + 7) / 8 * 8 * p.nsplit;
+  hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(kCmpThreads), 0, st, p);
   return hipGetLastError();
 }
 

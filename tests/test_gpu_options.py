@@ -202,3 +202,40 @@ def test_compression_branch_matches_oracle(d, G, kv, md):
             for g in range(G):
                 assert rel_l2(got_o[g], o[g]) <= 1e-5, (b, h, g, rel_l2(got_o[g], o[g]))
             np.testing.assert_allclose(got_l, l, rtol=0, atol=LSE_TOL * max(1.0, float(np.max(np.abs(l)))))
+
+
+# head splits of the branch's workgroups: 64 units of 16 heads take four heads
+# each, of 8 heads two, of 4 heads one; block counts around the pass of 256
+# (16 waves of 16 blocks; 128 for four heads of fp32 and E2M1 means at d = 128)
+@pytest.mark.parametrize("d,G,md", [(128, 16, "f32"), (128, 16, "bf16"), (128, 16, "e2m1"), (128, 8, "bf16"),
+                                    (64, 16, "e2m1"), (64, 8, "f32"), (64, 4, "bf16")])
+def test_compression_branch_head_splits(d, G, md):
+    T, B, Hkv, L = 32 * 300, 8, 8, 32
+    g = torch.Generator(device=DEV)
+    g.manual_seed(700 + G + d)
+    k, v = (torch.randn(B, Hkv, T, d, generator=g, device=DEV).to(torch.bfloat16) for _ in range(2))
+    q = torch.randn(B, G * Hkv, d, generator=g, device=DEV)
+    cfg = _cfg(d, 0, "bf16", md, "bf16", T, G=G, B=B, Hkv=Hkv, value_mean=True, block_size=L)
+    lens = [T, 32 * 256, 32 * 256 + 1, 32 * 128 + 5, 32 * 15, 33, 1, 0]
+    seq = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    rec = cobs.new_summaries(cfg, DEV)
+    say(f"compression branch head splits d={d} G={G} mean {md}")
+    cobs.cobs_build_block_stats(cfg, k, v, seq, rec)
+    out = torch.full((B, G * Hkv, d), 7.0, dtype=torch.float32, device=DEV)
+    lse = torch.full((B, G * Hkv), 7.0, dtype=torch.float32, device=DEV)
+    cobs.cobs_compression_branch(cfg, q, rec, seq, out, lse)
+    sync()
+    for b, Tb in enumerate(lens):
+        nb = -(-Tb // L)
+        for h in (0, 5):
+            gs = slice(h * G, (h + 1) * G)
+            got_o, got_l = out[b, gs].cpu().numpy(), lse[b, gs].cpu().numpy()
+            if nb == 0:
+                assert np.all(got_o == 0) and np.all(np.isneginf(got_l))
+                continue
+            cnt, mns, _, vmn = (R.decode(rec[b, h, :nb].cpu().numpy(), d, 0, md, "bf16", False, True)[i]
+                                for i in (0, 1, 2, -1))
+            o, l = M.compression_attention(f64(q[b, gs]), cnt, mns, vmn, cfg.scale)
+            for i in range(G):
+                assert rel_l2(got_o[i], o[i]) <= 1e-5, (b, h, i, rel_l2(got_o[i], o[i]))
+            np.testing.assert_allclose(got_l, l, rtol=0, atol=LSE_TOL * max(1.0, float(np.max(np.abs(l)))))
