@@ -81,13 +81,11 @@ __device__ __forceinline__ void store_vector_codes_wave(const float* x, int len,
       reinterpret_cast<uint32_t*>(dst)[e] = f32x2_to_bf16x2_rne(x[2 * e], x[2 * e + 1]);
     return;
   }
-  for (int e = lane; e < len / 8; e += 64) {
+  // two codes (one byte) per lane: all 64 lanes share the divisions
+  for (int e = lane; e < len / 2; e += 64) {
     uint32_t w = 0;
-    if (scale > 0.0f) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) w |= e2m1_code(x[8 * e + j], scale) << (4 * j);
-    }
-    reinterpret_cast<uint32_t*>(dst)[e] = w;
+    if (scale > 0.0f) w = e2m1_code(x[2 * e], scale) | (e2m1_code(x[2 * e + 1], scale) << 4);
+    dst[e] = (uint8_t)w;
   }
 }
 
@@ -127,6 +125,42 @@ __device__ __forceinline__ float row_bcast(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + C, 0xf, 0xf, true));
 }
 
+// acc[j] += (lane C + j's a of each row of 16) * b, j < N: multiply-adds with the
+// broadcast as their DPP operand (the compiler fuses broadcasts into products
+// and sums only).  A DPP operand may be read two wait states after its write:
+// each group starts with that wait.
+template <int C, int N>
+__device__ __forceinline__ void fmac_bcast(float* acc, float a, float b) {
+#define COBS_FMAC(i, c) "v_fmac_f32_dpp %" #i ", %[a], %[b] row_newbcast:%[" #c "] row_mask:0xf bank_mask:0xf\n\t"
+  if constexpr (N >= 4) {
+    __asm__("s_nop 1\n\t" COBS_FMAC(0, c0) COBS_FMAC(1, c1) COBS_FMAC(2, c2) COBS_FMAC(3, c3)
+            : "+&v"(acc[0]), "+&v"(acc[1]), "+&v"(acc[2]), "+&v"(acc[3])
+            : [a] "v"(a), [b] "v"(b), [c0] "n"(C), [c1] "n"(C + 1), [c2] "n"(C + 2), [c3] "n"(C + 3));
+    fmac_bcast<C + 4, N - 4>(acc + 4, a, b);
+  } else if constexpr (N > 0) {
+    __asm__("s_nop 1\n\t" COBS_FMAC(0, c0) : "+&v"(acc[0]) : [a] "v"(a), [b] "v"(b), [c0] "n"(C));
+    fmac_bcast<C + 1, N - 1>(acc + 1, a, b);
+  }
+#undef COBS_FMAC
+}
+
+// acc += sum_{m < N} (lane C's a[m] of each row of 16) * x[m], in order.
+template <int C, int N>
+__device__ __forceinline__ void dot_bcast(float& acc, const float* a, const float* x) {
+#define COBS_FMAC(i) "v_fmac_f32_dpp %0, %[a" #i "], %[x" #i "] row_newbcast:%[c] row_mask:0xf bank_mask:0xf\n\t"
+  if constexpr (N >= 4) {
+    __asm__("s_nop 1\n\t" COBS_FMAC(0) COBS_FMAC(1) COBS_FMAC(2) COBS_FMAC(3)
+            : "+&v"(acc)
+            : [a0] "v"(a[0]), [a1] "v"(a[1]), [a2] "v"(a[2]), [a3] "v"(a[3]), [x0] "v"(x[0]), [x1] "v"(x[1]),
+              [x2] "v"(x[2]), [x3] "v"(x[3]), [c] "n"(C));
+    dot_bcast<C, N - 4>(acc, a + 4, x + 4);
+  } else if constexpr (N > 0) {
+    __asm__("s_nop 1\n\t" COBS_FMAC(0) : "+&v"(acc) : [a0] "v"(a[0]), [x0] "v"(x[0]), [c] "n"(C));
+    dot_bcast<C, N - 1>(acc, a + 1, x + 1);
+  }
+#undef COBS_FMAC
+}
+
 template <int P>
 __device__ __forceinline__ void cholesky_inverse_lanes(const float* Sm, float* Lm, int lane);
 
@@ -145,45 +179,34 @@ __device__ __forceinline__ void cholesky_inverse(const float* Sm, float* Lm, int
     cholesky_inverse_lanes<P>(Sm, Lm, lane);
     return;
   }
-  float row[P];
+  float row[P];                          // row li of S', then -L[li][k] for li > k (0 otherwise)
   const int li = lane & 15;
   const float dl = Sm[li * (P + 1) + li];
   const float rnl = dl > 0.0f ? __builtin_amdgcn_rsqf(dl) : 0.0f;
-#pragma unroll
-  for (int c = 0; c < P; ++c) {
-    const float dc = Sm[c * (P + 1) + c];
-    const float rnc = dc > 0.0f ? __builtin_amdgcn_rsqf(dc) : 0.0f;
-    row[c] = Sm[li * (P + 1) + c] * rnl * rnc;
-  }
+  [&]<int... cs>(std::integer_sequence<int, cs...>) {
+    ((row[cs] = (Sm[li * (P + 1) + cs] * rnl) * row_bcast<cs>(rnl)), ...);
+  }(std::make_integer_sequence<int, P>{});
   const float thr = 1e-6f;
   float rdl = 0.0f;                      // 1 / L[li][li] (0 for a dropped column)
   auto step = [&](auto kc) {
     constexpr int k = decltype(kc)::value;
     const float piv = row_bcast<k>(row[k]);
-    const bool ok = piv > thr;
-    const float rdk = ok ? __builtin_amdgcn_rsqf(piv) : 0.0f;
-    const float dk = piv * rdk;
+    const float rdk = piv > thr ? __builtin_amdgcn_rsqf(piv) : 0.0f;
     rdl = (li == k) ? rdk : rdl;
     const float lk = (li > k) ? row[k] * rdk : 0.0f;        // L[li][k], 0 on and above the diagonal
-    const float nlk = -lk;
-    row[k] = (li == k) ? dk : ((li > k) ? lk : row[k]);
-    [&]<int... cs>(std::integer_sequence<int, cs...>) {
-      ((cs > k ? (void)(row[cs] = __builtin_fmaf(row_bcast<cs>(row[k]), nlk, row[cs])) : (void)0), ...);
-    }(std::make_integer_sequence<int, P>{});
+    row[k] = -lk;
+    fmac_bcast<k + 1, P - 1 - k>(row + k + 1, row[k], lk);
   };
   [&]<int... ks>(std::integer_sequence<int, ks...>) {
     (step(std::integral_constant<int, ks>{}), ...);
   }(std::make_integer_sequence<int, P>{});
   // X = L^-1 by forward substitution, lane c computing column c
-  float x[P], nx[P];
+  float x[P];
   auto fwd = [&](auto kc) {
     constexpr int k = decltype(kc)::value;
     float acc = (k == li) ? 1.0f : 0.0f;
-    [&]<int... ms>(std::integer_sequence<int, ms...>) {
-      ((ms < k ? (void)(acc = __builtin_fmaf(row_bcast<k>(row[ms]), nx[ms], acc)) : (void)0), ...);
-    }(std::make_integer_sequence<int, P>{});
+    dot_bcast<k, k>(acc, row, x);
     x[k] = acc * row_bcast<k>(rdl);
-    nx[k] = -x[k];
   };
   [&]<int... ks>(std::integer_sequence<int, ks...>) {
     (fwd(std::integral_constant<int, ks>{}), ...);

@@ -5,12 +5,13 @@
 // termination), laid out so that a wave needs no workgroup barrier and several
 // blocks stream through a CU at once.
 //
-//   * Lane (lk, lr) = (lane / 16, lane % 16) reads rows 16 t + lr of the block
-//     and the d / 4 columns [lk d/4, (lk+1) d/4), first for the column means
-//     (fp64 sums, reduced over the 16 lanes of a row group), then again,
-//     centred, as the operands of the Gram matrix: at k-step (chunk, e) lane
-//     group lk contributes column lk d/4 + 8 chunk + e, for every row tile as
-//     both A and B operand of v_mfma_f32_16x16x4_f32.
+//   * Lane (lk, lr) = (lane / 16, lane % 16) reads d / 16 columns of rows
+//     16 a + 4 lk + v for the column means (fp64 sums, the four lane groups' by
+//     lane swaps).  For the Gram matrix it reads rows 16 t + lr and the d / 4
+//     columns [lk d/4, (lk+1) d/4), centred: at k-step (chunk, e) lane group lk
+//     contributes column lk d/4 + 8 chunk + e, for every row tile as both A and
+//     B operand of v_mfma_f32_16x16x4_f32.  Only the tiles on and above the
+//     diagonal are formed; the others are their transposes.
 //   * The Gram matrix stays in registers in the MFMA result layout:
 //     g[t][u][v] = Gamma[16 t + 4 lk + v][16 u + lr].  By symmetry that is the
 //     A operand of Gamma W with the contraction index 16 a + 4 lk + v, and the
@@ -31,6 +32,12 @@
 //     result tile is the operand of one Gram k-step with the feature index
 //     permuted.  The factor pass forms Kc^T w / sqrt(n) as above, then
 //     xi_ss = U^T xi, on which the sign rule and the record work.
+//
+// What bounds it: instruction issue.  A block takes 13.6k vector and 1.4k matrix
+// instructions (62k and 40k cycles of a SIMD), which at twelve waves per CU fill
+// the SIMDs: 1,364 us for 32,768 blocks (d = 128, L = 64, r = 4, bf16 keys).  With
+// twice the registers (eight waves), broadcasts as moves of their own in the
+// Cholesky, all Gram tiles and sixteen-lane fp64 column sums it took 1,817.
 #pragma once
 
 #include "block_stats.h"
@@ -75,33 +82,39 @@ __device__ __forceinline__ void write_record_wave(const StatsArgs& p, uint8_t* R
   for (int idx = end / 4 + lane; idx < lay.total / 4; idx += 64) reinterpret_cast<uint32_t*>(R)[idx] = 0u;
 }
 
-// LDS of one wave (16-byte aligned pieces).  Gamma's bf16 parts kept in LDS
-// (the low part, or all three) live from the split of Gamma to the last
-// product of the power iteration; the Rayleigh-Ritz, Jacobi and factor
-// buffers, written after that product, take the same bytes.
+// LDS of one wave (16-byte aligned pieces): the rows of Y and the P x P matrix of
+// the power iteration, and behind them the parts of Gamma kept in LDS (the low
+// bf16 part, or all three), which live from the split of Gamma to the last
+// product of the power iteration.  The means take the first bytes while the
+// Gram matrix is formed (then registers), the Gram tiles being transposed the
+// same ones; the Rayleigh-Ritz, Jacobi and factor buffers, written after the last
+// product, take Gamma's.  At L = 64, d = 128 this is 13,632 bytes: twelve waves per CU.
 template <int D, int LB>
 struct WaveStatsLds {
   static constexpr int P = 16, PS = P + 1;
   static constexpr size_t al(size_t x) { return (x + 15) / 16 * 16; }
   static constexpr size_t mx(size_t a, size_t b) { return a > b ? a : b; }
-  static constexpr size_t mean = 0;                        // [D]
-  static constexpr size_t vmean = al(mean + 4 * D);        // [D]
-  static constexpr size_t yp = al(vmean + 4 * D);          // [LB][PS]: Y, then W, by rows
-  static constexpr size_t sm = al(yp + 4 * LB * PS);       // [P][PS]
-  static constexpr size_t lm = al(sm + 4 * P * PS);        // [P][PS]
-  static constexpr size_t misc = al(lm + 4 * P * PS);      // order[4], ritz[4], skew[4], trace
+  static constexpr size_t early_mean = 0;                  // [D] until the Gram matrix is formed
+  static constexpr size_t yp = 0;                          // [LB][PS]: Y, then W, by rows
+  static constexpr size_t sm = al(yp + 4 * LB * PS);       // [P][PS]: Y^T Y, then N X^T
+  static constexpr size_t gparts = al(sm + 4 * P * PS);
+  // Gram tiles (t, u), t < u, [16][PS] each, being transposed
+  static constexpr int NT16 = LB / 16;
+  static constexpr size_t tiles_end = 4 * 16 * PS * (size_t)(NT16 * (NT16 - 1) / 2);
   // one bf16 part of Gamma: [NT16][NT16 / 2][64 lanes] x 16 bytes
-  static constexpr size_t part_bytes = (size_t)(LB / 16) * (LB / 32) * 64 * 16;
-  static constexpr size_t gparts = al(misc + 4 * 16);
+  static constexpr size_t part_bytes = (size_t)NT16 * (NT16 / 2) * 64 * 16;
   static constexpr size_t hm = gparts;                     // [P][PS]
   static constexpr size_t vm = al(hm + 4 * P * PS);        // [P][PS]
-  static constexpr size_t wr = al(vm + 4 * P * PS);        // [4][LB] Ritz vectors
-  static constexpr size_t xi = al(wr + 4 * 4 * LB);        // [4][D] factors
-  static constexpr size_t chk = al(xi + 4 * 4 * D);        // Jacobi stop test: diagonal [P], ranks [P], threshold
+  static constexpr size_t xi = hm;                         // [4][D] factors, after the last reads of V
+  static constexpr size_t wr = al(mx(vm + 4 * P * PS, xi + 4 * 4 * D));   // [4][LB] Ritz vectors
+  static constexpr size_t chk = al(wr + 4 * 4 * LB);       // Jacobi stop test: diagonal [P], ranks [P], threshold
   static constexpr size_t xss = al(chk + 4 * (2 * P + 4)); // [4][<= D] subspace factors
-  static constexpr size_t late = al(xss + 4 * 4 * D);
-  static constexpr size_t bytes = mx(late, gparts + part_bytes);
-  static constexpr size_t bytes_glds = mx(late, gparts + 3 * part_bytes);
+  static constexpr size_t mean = al(xss + 4 * 4 * D);      // [D]
+  static constexpr size_t vmean = al(mean + 4 * D);        // [D]
+  static constexpr size_t misc = al(vmean + 4 * D);        // order[4], ritz[4], skew[4]
+  static constexpr size_t late = al(misc + 4 * 16);
+  static constexpr size_t bytes = al(mx(mx(late, gparts + part_bytes), tiles_end));
+  static constexpr size_t bytes_glds = al(mx(bytes, gparts + 3 * part_bytes));
 };
 
 template <int D, int LB, bool GLDS = false>
@@ -139,17 +152,20 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
   constexpr int NT16 = LB / 16;                 // 16-row tiles of the block
   constexpr int CPL = D / 4;                    // columns of a lane group
   constexpr int NCH = CPL / 8;                  // 8-column chunks of a lane group
-  constexpr int EPL = D / 64;                   // factor columns of a lane
+  constexpr int EPL = D / 64;                   // columns of a lane (skew)
+  constexpr int FPR = D / 16;                   // features of a lane in the projection Z
   float* mean = reinterpret_cast<float*>(pool + Lay::mean);
   float* vmean = reinterpret_cast<float*>(pool + Lay::vmean);
   float* Yp = reinterpret_cast<float*>(pool + Lay::yp);
   float* Sm = reinterpret_cast<float*>(pool + Lay::sm);
-  float* Lm = reinterpret_cast<float*>(pool + Lay::lm);
+  float* Lm = Sm;                        // (read whole before it is written)
   float* Hm = reinterpret_cast<float*>(pool + Lay::hm);
   float* Vm = reinterpret_cast<float*>(pool + Lay::vm);
+  float* Wr = reinterpret_cast<float*>(pool + Lay::wr);
+  float* Gt = reinterpret_cast<float*>(pool);
+  float* early_mean = reinterpret_cast<float*>(pool + Lay::early_mean);
   float* cdiag = reinterpret_cast<float*>(pool + Lay::chk);
   int* crank = reinterpret_cast<int*>(pool + Lay::chk) + P;
-  float* Wr = reinterpret_cast<float*>(pool + Lay::wr);
   float* Xi = reinterpret_cast<float*>(pool + Lay::xi);
   float* Xs = reinterpret_cast<float*>(pool + Lay::xss);
   const float* Uh = SS ? p.basis + (size_t)h * D * FD : nullptr;
@@ -160,36 +176,27 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
   const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
   const int r = p.r;
 
-  // 8 columns lk CPL + 8 q .. + 7 of rows 16 t + lr (zero past the block's n
-  // rows), as raw words (the loads in flight) and then as floats
-  struct Raw {
-    uint4 w[KF32 ? 2 : 1];
-  };
   // the block's first token and the stride between its tokens (a page holds
   // one block); kbase < 0: its page is outside the pool (zero keys)
   const int64_t kbase = kv_offset(p.kv, b, h, j * LB);
   const int64_t rs = p.kv.table ? (int64_t)p.kv.d : p.kv.st;
-  int64_t roff[NT16];                           // row offsets, -1: no row
-#pragma unroll
-  for (int t = 0; t < NT16; ++t) {
-    const int i = 16 * t + lr;
-    roff[t] = (i < n && kbase >= 0) ? kbase + i * rs : -1;
-  }
+  constexpr int ES = KF32 ? 4 : 2;
+  // byte offset of row i from the block's first token (at most 128 rows of
+  // 2^24 bytes): loads take a wave-uniform base and one 32-bit offset per lane
+  const int rsb = (int)rs * ES;
+  const int64_t kb0 = kbase < 0 ? 0 : kbase;
+  // 8 columns lk CPL + 8 q .. + 7 of rows 16 t + lr of a full block, as raw
+  // words (the loads in flight) and then as floats
+  struct Raw {
+    uint4 w[KF32 ? 2 : 1];
+  };
+  const int col_off = lr * rsb + lk * CPL * ES;
   auto load_raw = [&](const void* base, int q, Raw* raw) {
 #pragma unroll
     for (int t = 0; t < NT16; ++t) {
-      if (roff[t] >= 0) {
-        if constexpr (KF32) {
-          const uint4* src = reinterpret_cast<const uint4*>(static_cast<const float*>(base) + roff[t] + lk * CPL + 8 * q);
-          raw[t].w[0] = src[0];
-          raw[t].w[1] = src[1];
-        } else {
-          raw[t].w[0] = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(base) + roff[t] + lk * CPL + 8 * q);
-        }
-      } else {
+      const char* src = static_cast<const char*>(base) + kb0 * ES + (16 * t * rsb + 8 * q * ES);
 #pragma unroll
-        for (int k = 0; k < (KF32 ? 2 : 1); ++k) raw[t].w[k] = make_uint4(0u, 0u, 0u, 0u);
-      }
+      for (int k = 0; k < (KF32 ? 2 : 1); ++k) raw[t].w[k] = *reinterpret_cast<const uint4*>(src + col_off + 16 * k);
     }
   };
   auto unpack = [&](const Raw* raw, float (*x)[8]) {
@@ -208,39 +215,102 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
       }
     }
   };
-  // column means into LDS: fp64 sums (exact for the block's fp32 values unless
-  // their magnitudes span > 2^29), one rounding to fp32, so a block of
-  // identical rows centres to exact zeros
-  // (the loads of QB chunks in flight together: all of them for bf16 keys)
-  constexpr int QB = KF32 ? (NCH > 1 ? NCH / 2 : 1) : NCH;
-  auto column_mean = [&](const void* base, float* out) {
+  // Lane (lk, lr) of the row layout reads features FPR lr .. of rows 16 a + 4 lk + v
+  // (a load instruction reads four whole rows)
+  constexpr int ZW = KF32 ? FPR : FPR / 2;      // words of a lane's features
+  auto load_words_at = [&](const char* src, uint32_t* w) {
+    if constexpr (ZW == 2) {
+      const uint2 u = *reinterpret_cast<const uint2*>(src);
+      w[0] = u.x; w[1] = u.y;
+    } else {
 #pragma unroll
-    for (int q0 = 0; q0 < NCH; q0 += QB) {
-      Raw raw[QB][NT16];
-#pragma unroll
-      for (int q = 0; q < QB; ++q) load_raw(base, q0 + q, raw[q]);
-#pragma unroll
-      for (int q = 0; q < QB; ++q) {
-        float x[NT16][8];
-        unpack(raw[q], x);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          double cs = 0.0;
-#pragma unroll
-          for (int t = 0; t < NT16; ++t) cs += (double)x[t][e];
-          cs = row16_sum_last(cs);
-          if (lr == 15) out[lk * CPL + 8 * (q0 + q) + e] = (float)(cs / (double)n);
-        }
+      for (int q = 0; q < ZW; q += 4) {
+        const uint4 u = *reinterpret_cast<const uint4*>(src + 4 * q);
+        w[q] = u.x; w[q + 1] = u.y; w[q + 2] = u.z; w[q + 3] = u.w;
       }
     }
-    wave_lds_sync();
   };
-  column_mean(p.kv.k, mean);
-  if (p.vmean) column_mean(p.kv.v, vmean);
+  const int row_off = 4 * lk * rsb + FPR * lr * ES;
+  auto load_rows4 = [&](const void* base, int a, uint32_t (*kw)[ZW]) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      load_words_at(static_cast<const char*>(base) + kb0 * ES + (16 * a + v) * rsb + row_off, kw[v]);
+  };
+  // the same for a partial block or one whose page is outside the pool: rows
+  // without a key read a valid row and give zeros
+  auto load_rows4_masked = [&](const void* base, int a, uint32_t (*kw)[ZW]) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int row = 16 * a + 4 * lk + v;
+      load_words_at(static_cast<const char*>(base) + kb0 * ES + min(row, n - 1) * rsb + FPR * lr * ES, kw[v]);
+      const uint32_t mask = (row < n && kbase >= 0) ? ~0u : 0u;
+#pragma unroll
+      for (int q = 0; q < ZW; ++q) kw[v][q] &= mask;
+    }
+  };
+  auto feature = [&](const uint32_t* w, int e) -> float {
+    return KF32 ? __uint_as_float(w[KF32 ? e : 0]) : (e % 2 ? bf16_hi(w[e / 2]) : bf16_lo(w[e / 2]));
+  };
+  // column means into LDS: fp64 sums (exact for the block's fp32 values unless
+  // their magnitudes span > 2^29), one rounding to fp32, so a block of
+  // identical rows centres to exact zeros.  A lane adds its rows; the four lane
+  // groups' sums meet by lane swaps.
+  const bool whole = n == LB && kbase >= 0;
+  constexpr int QB = (KF32 && NT16 > 2) ? NT16 / 2 : NT16;     // row tiles in flight together
+  auto column_mean = [&](const void* base, float* m) {
+    double cs[FPR];
+#pragma unroll
+    for (int e = 0; e < FPR; ++e) cs[e] = 0.0;
+    auto add = [&](const uint32_t (*kw)[ZW]) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int e = 0; e < FPR; ++e) cs[e] += (double)feature(kw[v], e);
+    };
+    if (whole) {
+#pragma unroll
+      for (int a0 = 0; a0 < NT16; a0 += QB) {
+        uint32_t kw[QB][4][ZW];
+#pragma unroll
+        for (int a = 0; a < QB; ++a) load_rows4(base, a0 + a, kw[a]);
+#pragma unroll
+        for (int a = 0; a < QB; ++a) add(kw[a]);
+      }
+    } else {
+#pragma unroll 1
+      for (int a = 0; a < NT16; ++a) {
+        uint32_t kw[4][ZW];
+        load_rows4_masked(base, a, kw);
+        add(kw);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < FPR; ++e) cs[e] = row_groups_sum(cs[e]);
+    // (for a full block the division is by a power of two)
+    if (n == LB) {
+#pragma unroll
+      for (int e = 0; e < FPR; ++e) m[e] = (float)(cs[e] * (1.0 / LB));
+    } else {
+#pragma unroll
+      for (int e = 0; e < FPR; ++e) m[e] = (float)(cs[e] / (double)n);
+    }
+  };
+  // a lane's FPR means into LDS
+  auto put_mean = [&](const float* m, float* out) {
+    if (lk == 0) {
+#pragma unroll
+      for (int e = 0; e < FPR; ++e) out[FPR * lr + e] = m[e];
+    }
+  };
+  float kmean[FPR];
+  column_mean(p.kv.k, kmean);
 
-  const bool factors = (n == LB) && (r > 0);
+  // (zero keys have zero factors)
+  const bool factors = whole && r > 0;
   uint8_t* R = p.rec + (((int64_t)b * p.hkv + h) * p.nbmax + j) * p.lay.total;
   if (factors) {
+    put_mean(kmean, early_mean);
+    wave_lds_sync();
     // ---- Gram matrix Kc Kc^T (subspace: (Kc U)(Kc U)^T):
     // g[t][u][v] = Gamma[16 t + 4 lk + v][16 u + lr]
     f32x4_t g[NT16][NT16];
@@ -269,8 +339,8 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
       if (q + 1 < NCH) load_raw(p.kv.k, q + 1, rnext);
       float x[NT16][8];
       unpack(rcur, x);
-      const float4 m0 = *reinterpret_cast<const float4*>(mean + lk * CPL + 8 * q);
-      const float4 m1 = *reinterpret_cast<const float4*>(mean + lk * CPL + 8 * q + 4);
+      const float4 m0 = *reinterpret_cast<const float4*>(early_mean + lk * CPL + 8 * q);
+      const float4 m1 = *reinterpret_cast<const float4*>(early_mean + lk * CPL + 8 * q + 4);
       const float mm[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
 #pragma unroll
       for (int t = 0; t < NT16; ++t)
@@ -294,7 +364,7 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
 #pragma unroll
           for (int t = 0; t < NT16; ++t)
 #pragma unroll
-            for (int u = 0; u < NT16; ++u)
+            for (int u = t; u < NT16; ++u)
               g[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t][e], x[u][e], g[t][u], 0, 0, 0);
       }
     }
@@ -308,8 +378,28 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
 #pragma unroll
           for (int t = 0; t < NT16; ++t)
 #pragma unroll
-            for (int u = 0; u < NT16; ++u)
+            for (int u = t; u < NT16; ++u)
               g[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(kp[a][t][v], kp[a][u][v], g[t][u], 0, 0, 0);
+    }
+    // the tiles below the diagonal, transposed through LDS
+    {
+      wave_lds_sync();                   // the last reads of the means
+      int k = 0;
+#pragma unroll
+      for (int t = 0; t < NT16; ++t)
+#pragma unroll
+        for (int u = t + 1; u < NT16; ++u, ++k)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) Gt[(16 * k + 4 * lk + v) * PS + lr] = g[t][u][v];
+      wave_lds_sync();
+      k = 0;
+#pragma unroll
+      for (int t = 0; t < NT16; ++t)
+#pragma unroll
+        for (int u = t + 1; u < NT16; ++u, ++k)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) g[u][t][v] = Gt[(16 * k + lr) * PS + 4 * lk + v];
+      wave_lds_sync();
     }
     float diag = 0.0f;
 #pragma unroll
@@ -322,11 +412,11 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
     const float trace = wave_sum_rows(diag);
     const float gsc = trace > 0.0f ? 1.0f / trace : 0.0f;
 
-    // Gamma as three bf16 parts (hi + mid + lo = the fp32 value) in the bf16
-    // matrix-core operand layout: for output tile t and k-chunk c, lane group
-    // lk supplies the contraction indices 16 a + 4 lk + v, a in {2c, 2c + 1}.
-    // The low part, which only the last product takes, is kept in LDS (GLDS:
-    // all three).
+    // Gamma as bf16 parts in the bf16 matrix-core operand layout: for output
+    // tile t and k-chunk c, lane group lk supplies the contraction indices
+    // 16 a + 4 lk + v, a in {2c, 2c + 1}.  Three parts, hi + mid + lo = the fp32
+    // value; the low one, which only the last product takes, is kept in LDS
+    // (GLDS: all three).
     constexpr int KC = NT16 / 2;                  // 32-index k-chunks
     sbf16x8_t gp[GLDS ? 1 : 2][GLDS ? 1 : NT16][GLDS ? 1 : KC];
     sbf16x8_t* gpl = reinterpret_cast<sbf16x8_t*>(pool + Lay::gparts);
@@ -356,37 +446,27 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
     // error ~4e-3, which the later products damp out of the subspace), the
     // next ones the three leading cross terms (~1e-5), and the last product,
     // which feeds the Rayleigh-Ritz step, all terms down to 2^-24.
-    auto product = [&](const f32x4_t* src, f32x4_t* dst, int terms) {
-      sbf16x8_t wp[KC][3];
+    auto product = [&](auto nterms, const f32x4_t* src, f32x4_t* dst) {
+      constexpr int terms = decltype(nterms)::value, NW = terms == 6 ? 3 : terms == 3 ? 2 : 1;
+      sbf16x8_t wp[KC][NW];
 #pragma unroll
       for (int c = 0; c < KC; ++c) {
         float x[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) x[i] = src[2 * c + i / 4][i % 4];
-        if (terms == 6) {
-          split_bf16x8<3>(x, wp[c]);
-        } else if (terms == 3) {
-          sbf16x8_t two[2];
-          split_bf16x8<2>(x, two);
-          wp[c][0] = two[0];
-          wp[c][1] = two[1];
-        } else {
-          sbf16x8_t one[1];
-          split_bf16x8<1>(x, one);
-          wp[c][0] = one[0];
-        }
+        split_bf16x8<NW>(x, wp[c]);
       }
 #pragma unroll
       for (int t = 0; t < NT16; ++t) {
         f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int c = 0; c < KC; ++c) {
-          if (terms == 6) {
+          if constexpr (terms == 6) {
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gpart(2, t, c), wp[c][0], acc, 0, 0, 0);
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gpart(1, t, c), wp[c][1], acc, 0, 0, 0);
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gpart(0, t, c), wp[c][2], acc, 0, 0, 0);
           }
-          if (terms >= 3) {
+          if constexpr (terms >= 3) {
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gpart(1, t, c), wp[c][0], acc, 0, 0, 0);
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gpart(0, t, c), wp[c][1], acc, 0, 0, 0);
           }
@@ -396,6 +476,9 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
         for (int v = 0; v < 4; ++v) dst[t][v] = acc[v] * gsc;
       }
     };
+    constexpr std::integral_constant<int, 1> coarse{};
+    constexpr std::integral_constant<int, 3> finer{};
+    constexpr std::integral_constant<int, 6> all_terms{};
     // X^T Y (P x P) into out (row stride PS), X and Y in the result layout
     auto small_gram = [&](const f32x4_t* X, const f32x4_t* Y, float* out) {
       f32x4_t acc0 = {0.0f, 0.0f, 0.0f, 0.0f}, acc1 = acc0;
@@ -418,21 +501,8 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
     };
 
     f32x4_t w[NT16], y[NT16];
-#pragma unroll
-    for (int a = 0; a < NT16; ++a)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) w[a][v] = init_sign(16 * a + 4 * lk + v, lr);
-#pragma unroll 1
-    for (int it = 0; it <= kPowerIters; ++it) {
-      const int terms = it == kPowerIters ? 6 : (it < kHiIters ? 1 : 3);
-      product(w, y, terms);
-      if (it == kPowerIters) break;      // the last product feeds the Rayleigh-Ritz step
-      if (it >= kSinglePowerIters) {       // Gamma^2 W (W is replaced below)
-        product(y, w, terms);
-#pragma unroll
-        for (int t = 0; t < NT16; ++t) y[t] = w[t];
-      }
-      // ---- W = Y N X^T, the Cholesky-QR of Y
+    // W = Y N X^T, the Cholesky-QR of Y
+    auto orthonormalise = [&]() {
       small_gram(y, y, Sm);
       to_rows(y);
       wave_lds_sync();
@@ -448,9 +518,31 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
         w[t] = acc;
       }
       wave_lds_sync();                   // Yp, Sm and Lm are rewritten by the next iteration
+    };
+#pragma unroll
+    for (int a = 0; a < NT16; ++a)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) w[a][v] = init_sign(16 * a + 4 * lk + v, lr);
+#pragma unroll 1
+    for (int it = 0; it <= kPowerIters; ++it) {
+      if (it == kPowerIters) {             // the last product feeds the Rayleigh-Ritz step
+        product(all_terms, w, y);
+        break;
+      }
+      if (it < kHiIters) product(coarse, w, y);
+      else product(finer, w, y);
+      if (it >= kSinglePowerIters) {       // Gamma^2 W (W is replaced below)
+        if (it < kHiIters) product(coarse, y, w);
+        else product(finer, y, w);
+#pragma unroll
+        for (int t = 0; t < NT16; ++t) y[t] = w[t];
+      }
+      orthonormalise();
     }
 
-    // ---- Rayleigh-Ritz: H = W^T (Gamma W), symmetrised; V = I
+    // ---- Rayleigh-Ritz: H = W^T (Gamma W), symmetrised; V = I (the buffers from
+    // here on take the place of Gamma's parts)
+    put_mean(kmean, mean);
     small_gram(w, y, Sm);
     to_rows(w);                          // W by rows, for the Ritz vectors
     wave_lds_sync();
@@ -470,8 +562,6 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
     // same layout.  By symmetry H's layout is also the A operand of H J.
     // Each lane forms its column's rotation from H's entries, which it takes
     // from the lanes holding them by lane permutes.
-    auto slot_index = [&](int m, int rnd) { return m == 0 ? 0 : 1 + (m - 1 + rnd) % (P - 1); };
-    auto index_slot = [&](int x, int rnd) { return x == 0 ? 0 : 1 + (x - 1 + (P - 1) - rnd) % (P - 1); };
     f32x4_t hr, vt;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -522,14 +612,19 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
 #pragma unroll 1
     for (int sweep = 0; sweep < kJacobiSweeps; ++sweep) {
       if (top_settled()) break;
-      bool moved = false;
+      uint64_t moved = 0;
+      int slot = lr - 1;                 // index lr's slot - 1 (lr > 0): one less each round, mod P - 1
 #pragma unroll 1
       for (int rnd = 0; rnd < P - 1; ++rnd) {
         // the round's pair of this lane's column: (pp, qq), lr's partner py.
         // The diagonal entry of column y sits in lane 16 (y / 4) + y, register
         // y % 4; H[pp][qq] in lane 16 (pp / 4) + qq, register pp % 4 (there the
         // column's partner's register).  Every lane forms its pair's rotation.
-        const int py = slot_index(P - 1 - index_slot(lr, rnd), rnd);
+        // (slots slot + 1 and P - 2 - slot; slot P - 1 pairs with index 0)
+        int px = lr == 0 ? P - 2 + rnd : P - 3 - slot + rnd;
+        px = px >= P - 1 ? px - (P - 1) : px;
+        const int py = (lr != 0 && slot == P - 2) ? 0 : 1 + px;
+        slot = slot == 0 ? P - 2 : slot - 1;
         const int pp = min(lr, py), qq = max(lr, py);
         auto reg = [&](int k) { return k == 0 ? hr[0] : k == 1 ? hr[1] : k == 2 ? hr[2] : hr[3]; };
         const float dsel = reg(lr & 3), osel = reg(py & 3);
@@ -539,7 +634,8 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
         const float app = from(dsel, 16 * (pp >> 2) + pp);
         const float aqq = from(dsel, 16 * (qq >> 2) + qq);
         const float apq = from(osel, 16 * (pp >> 2) + qq);
-        const bool big = fabsf(apq) > 1e-6f * sqrtf(fmaxf(app, 0.0f) * fmaxf(aqq, 0.0f)) && fabsf(apq) > 2e-8f;
+        const bool big =
+            fabsf(apq) > fmaxf(1e-6f * __builtin_amdgcn_sqrtf(fmaxf(app, 0.0f) * fmaxf(aqq, 0.0f)), 2e-8f);
         float c = 1.0f, sn = 0.0f;
         if (apq != 0.0f) {
           const float th = (aqq - app) * __builtin_amdgcn_rcpf(2.0f * apq);
@@ -547,7 +643,7 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
           c = __builtin_amdgcn_rsqf(tt * tt + 1.0f);
           sn = tt * c;
         }
-        moved = moved || __ballot(big) != 0;
+        moved |= __ballot(big);
         // J[x][y]: c on the diagonal; at y = partner(x), -s if y < x else s
         f32x4_t jr;
 #pragma unroll
@@ -566,7 +662,7 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
         hr = h2;
         vt = v2;
       }
-      if (!moved) break;
+      if (moved == 0) break;
     }
     // the eigenvalues on H's diagonal, V = (V^T)^T by rows, for the ranking and the Ritz vectors
 #pragma unroll
@@ -612,30 +708,26 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
       for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int c = 0; c < EPL; ++c) xs[i][c] = 0.0f;
-      // the lane's columns of 16 rows at a time, their loads in flight
-      // together (a block whose page is outside the pool reads page 0, which
-      // always exists, and masks the words to zero keys)
-      const uint32_t kmask = kbase < 0 ? 0u : ~0u;
-      const int64_t kb0 = kbase < 0 ? 0 : kbase;
+      // the lane's columns of 16 rows at a time, their loads in flight together
 #pragma unroll 1
       for (int r0 = 0; r0 < LB; r0 += 16) {
         float kv_[16][EPL];
 #pragma unroll
         for (int rr = 0; rr < 16; ++rr) {
-          const int64_t off = kb0 + (r0 + rr) * rs + EPL * lane;
+          const int64_t off = kbase + (r0 + rr) * rs + EPL * lane;
           if constexpr (KF32) {
             if constexpr (EPL == 2) {
               const uint2 a = *reinterpret_cast<const uint2*>(static_cast<const float*>(p.kv.k) + off);
-              kv_[rr][0] = __uint_as_float(a.x & kmask); kv_[rr][1] = __uint_as_float(a.y & kmask);
+              kv_[rr][0] = __uint_as_float(a.x); kv_[rr][1] = __uint_as_float(a.y);
             } else {
-              kv_[rr][0] = __uint_as_float(reinterpret_cast<const uint32_t*>(p.kv.k)[off] & kmask);
+              kv_[rr][0] = __uint_as_float(reinterpret_cast<const uint32_t*>(p.kv.k)[off]);
             }
           } else {
             if constexpr (EPL == 2) {
-              const uint32_t a = *reinterpret_cast<const uint32_t*>(static_cast<const uint16_t*>(p.kv.k) + off) & kmask;
+              const uint32_t a = *reinterpret_cast<const uint32_t*>(static_cast<const uint16_t*>(p.kv.k) + off);
               kv_[rr][0] = bf16_lo(a); kv_[rr][1] = bf16_hi(a);
             } else {
-              kv_[rr][0] = __uint_as_float(((uint32_t)static_cast<const uint16_t*>(p.kv.k)[off] << 16) & kmask);
+              kv_[rr][0] = __uint_as_float((uint32_t)static_cast<const uint16_t*>(p.kv.k)[off] << 16);
             }
           }
         }
@@ -773,15 +865,11 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
         }
       }
       if (lane < LB) {
-        const int64_t off0 = kbase < 0 ? -1 : kbase + lane * rs;
-        const int64_t off = off0 < 0 ? 0 : off0;
+        const int64_t off = kbase + lane * rs;
 #pragma unroll 1
         for (int e0 = 0; e0 < D; e0 += 8) {
           float kk[8];
-          if (off0 < 0) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) kk[e] = 0.0f;
-          } else if constexpr (KF32) {
+          if constexpr (KF32) {
             const float4* src = reinterpret_cast<const float4*>(static_cast<const float*>(p.kv.k) + off + e0);
             const float4 a = src[0], c = src[1];
             kk[0] = a.x; kk[1] = a.y; kk[2] = a.z; kk[3] = a.w; kk[4] = c.x; kk[5] = c.y; kk[6] = c.z; kk[7] = c.w;
@@ -812,6 +900,13 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
     }
   }
 
+  if (!factors) put_mean(kmean, mean);
+  if (p.vmean) {
+    float m[FPR];
+    column_mean(p.kv.v, m);
+    put_mean(m, vmean);
+  }
+  wave_lds_sync();
   write_record_wave<D, FD>(p, R, n, factors ? r : 0, mean, SS ? Xs : Xi, vmean, skw, lane);
 }
 

@@ -42,16 +42,28 @@ __global__ __launch_bounds__(kBuildThreads) void build_stats_kernel(BuildParams 
   block_stats<D, P, LB, KF32, SS>(a, b, h, j, min(LB, T - j * LB), pool);
 }
 
+template <size_t A, size_t B>
+constexpr size_t size_max() { return A > B ? A : B; }
+
+// Waves per SIMD that the registers are fitted to: the routine is bound by
+// issue and by the latencies of its serial parts, so more blocks in flight pay
+// up to what LDS holds (twelve waves per CU at L = 64, sixteen at L = 32);
+// subspace factors of fp32 keys hold too many projected keys for three.  The
+// step's single newest block (NT = 256) has the SIMD to itself.
+template <int D, int LB, bool KF32, int FD, int NT>
+constexpr int wave_build_waves() {
+  if (NT > 64) return 2;
+  if (LB == 32) return FD < D ? 3 : 4;
+  return (FD < D && KF32) ? 2 : 3;
+}
+
 // One wave per (batch row, KV head, block) of LB tokens: the configurations
 // of block_stats_wave (FD < D: subspace factors).  NT = 256: the decode step's
 // build with subspace factors, whose four waves first project the queries
 // (project_unit); then a partial newest block's means by all of them
 // (block_mean_wg, bitwise the wave routine's record), a full one by wave 0.
-template <size_t A, size_t B>
-constexpr size_t size_max() { return A > B ? A : B; }
-
 template <int D, int LB, bool KF32, int FD = D, int NT = 64>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void build_stats_wave_kernel(BuildParams p) {
+__global__ __launch_bounds__(NT, (wave_build_waves<D, LB, KF32, FD, NT>())) void build_stats_wave_kernel(BuildParams p) {
   constexpr size_t kPool = wave_stats_lds_bytes<D, LB>();
   constexpr size_t kProj = NT > 64 ? size_max<sizeof(float) * kProjectLdsFloats, block_mean_lds_bytes<D>()>() : 0;
   __shared__ __align__(16) char pool[size_max<kPool, kProj>()];

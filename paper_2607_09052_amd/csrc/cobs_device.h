@@ -325,20 +325,15 @@ __device__ __forceinline__ float wave_max_rows(float x) {
   return fmaxf(fmaxf(a, b), fmaxf(c, d));
 }
 
-// fp64 sum over each row of 16 lanes by shifted partial sums (DPP row_shr on
-// both halves); lane 15 of the row holds the total.  Every lane must be active.
-__device__ __forceinline__ double row16_sum_last(double x) {
-  auto shr = [](double v, auto nc) -> double {
-    constexpr int n = decltype(nc)::value;
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x110 + n, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x110 + n, 0xF, 0xF, true);
-    return __hiloint2double(hi, lo);
+// fp64 sum of the lanes l, l ^ 16, l ^ 32, l ^ 48 (the same lane of the four rows
+// of 16), in every one of them: swaps of odd and even rows, then of halves.
+__device__ __forceinline__ double row_groups_sum(double x) {
+  auto pairsum = [](double v, auto swap) -> double {
+    const auto lo = swap((uint32_t)__double2loint(v)), hi = swap((uint32_t)__double2hiint(v));
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
   };
-  x += shr(x, std::integral_constant<int, 1>{});
-  x += shr(x, std::integral_constant<int, 2>{});
-  x += shr(x, std::integral_constant<int, 4>{});
-  x += shr(x, std::integral_constant<int, 8>{});
-  return x;
+  x = pairsum(x, [](uint32_t u) { return __builtin_amdgcn_permlane16_swap(u, u, false, false); });
+  return pairsum(x, [](uint32_t u) { return __builtin_amdgcn_permlane32_swap(u, u, false, false); });
 }
 
 __device__ __forceinline__ float row16_sum(float x) {

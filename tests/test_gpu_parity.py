@@ -562,6 +562,36 @@ def test_build_stats_matches_oracle(law, d, r, L):
                 assert factors[blk, i][np.argmax(np.abs(factors[blk, i]))] > 0
 
 
+def _spectrum_keys(law, L, d, seed):
+    """Keys whose covariance has a given shape: the step plan of the one-wave
+    solver follows the spectrum (few steps for a clear gap, the most for a flat
+    one, the plain ones when columns of its basis drop out)."""
+    rng = np.random.default_rng(seed)
+    s = {"decay0.2": 0.2 ** (np.arange(d) / 2.0), "decay0.5": 0.5 ** (np.arange(d) / 2.0),
+         "decay0.8": 0.8 ** (np.arange(d) / 2.0), "flat": np.ones(d),
+         "plateau": np.where(np.arange(d) < 20, 1.0, 0.3), "rank3": np.where(np.arange(d) < 3, 1.0, 0.0),
+         "spikes": np.concatenate([[30.0, 10.0, 3.0, 1.0], np.full(d - 4, 0.05)])}[law]
+    q, _ = np.linalg.qr(rng.standard_normal((d, d)))
+    return ((rng.standard_normal((L, d)) * np.maximum(s, 1e-8)) @ q + 0.3 * rng.standard_normal(d)).astype(np.float32)
+
+
+@pytest.mark.parametrize("law", ["decay0.2", "decay0.5", "decay0.8", "flat", "plateau", "rank3", "spikes"])
+@pytest.mark.parametrize("d,r,L", [(128, 4, 64), (128, 1, 64), (64, 3, 64), (128, 4, 32), (64, 2, 32)])
+def test_build_stats_over_spectra(law, d, r, L):
+    nblk = 8
+    K = np.concatenate([_spectrum_keys(law, L, d, 31 * i + L + d) for i in range(nblk)])
+    k = torch.from_numpy(K).view(1, 1, nblk * L, d)
+    cfg = _cfg(batch=1, num_q_heads=1, num_kv_heads=1, head_dim=d, max_seq_len=nblk * L, rank=r, kv_dtype="f32",
+               block_size=L)
+    say(f"build spectrum {law} d={d} r={r} L={L}")
+    rec = cobs.new_summaries(cfg, DEV)
+    cobs.cobs_build_block_stats(cfg, k.to(DEV), k.to(DEV), torch.tensor([nblk * L], dtype=torch.int32, device=DEV), rec)
+    sync()
+    _, _, factors = R.decode(rec[0, 0].cpu().numpy(), d, r, "f32", "f32")
+    for blk in range(nblk):
+        ky_fan_checks(factors[blk], K[blk * L:blk * L + L].astype(np.float64), L, r)
+
+
 def test_build_bf16_keys_and_storage_dtypes_consistent():
     """bf16 keys; every storage dtype pair encodes the same fp32 statistics.
 
