@@ -218,94 +218,122 @@ __device__ __forceinline__ void cholesky_inverse(const float* Sm, float* Lm, int
   }
 }
 
-// The same for P = 32 (two rows of 16 lanes): lane k < P holds row k of L,
-// entries pass by lane reads into scalar registers.
+// The same for P = 32 by lanes 0..31 (32..63 the same again): lane k holds row k
+// of L, so the entries L[c][k] come from the first row of 16 lanes for c < 16 and
+// from the second for c >= 16.  The second row's updates with entries of the
+// first take a copy of them (lane swap); the first row's lanes need none of the
+// second's in the factorisation (c > k > their index: not read), and in the
+// substitution a copy of its rows.
 template <int P>
 __device__ __forceinline__ void cholesky_inverse_lanes(const float* Sm, float* Lm, int lane) {
-  float row[P], rn[P];
-  const int li = lane < P ? lane : 0;
+  static_assert(P == 32, "two rows of 16 lanes");
+  auto lane_of = [](float x, int k) -> float {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), k));
+  };
+  // the first / second row's lanes in both rows (and the same of the upper half)
+  auto first_row = [](float x) -> float {
+    return __uint_as_float(__builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false)[0]);
+  };
+  auto second_row = [](float x) -> float {
+    return __uint_as_float(__builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false)[1]);
+  };
+  float row[P];                          // row li of S', then -L[li][k] for li > k (0 otherwise)
+  const int li = lane & (P - 1);
+  const float dl = Sm[li * (P + 1) + li];
+  const float rnl = dl > 0.0f ? 1.0f / sqrtf(dl) : 0.0f;
 #pragma unroll
-  for (int c = 0; c < P; ++c) {
-    const float dc = Sm[c * (P + 1) + c];
-    rn[c] = dc > 0.0f ? 1.0f / sqrtf(dc) : 0.0f;
-  }
-  float rnl = rn[0];
-#pragma unroll
-  for (int c = 1; c < P; ++c) rnl = (c == li) ? rn[c] : rnl;
-#pragma unroll
-  for (int c = 0; c < P; ++c) row[c] = Sm[li * (P + 1) + c] * rnl * rn[c];
+  for (int c = 0; c < P; ++c) row[c] = Sm[li * (P + 1) + c] * rnl * lane_of(rnl, c);
   const float thr = 1e-6f;
-  float rd[P];
-#pragma unroll
-  for (int k = 0; k < P; ++k) {
-    const float piv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(row[k]), k));
-    const bool ok = piv > thr && piv > 0.0f;
-    const float dk = ok ? sqrtf(piv) : 0.0f;
-    const float rdk = ok ? 1.0f / dk : 0.0f;
-    rd[k] = rdk;
-    if (lane > k) row[k] *= rdk;
-    if (lane == k) row[k] = dk;
-#pragma unroll
-    for (int c = k + 1; c < P; ++c) {
-      const float lck = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(row[k]), c));
-      if (lane > k) row[c] -= row[k] * lck;
-    }
-  }
+  float rdl = 0.0f;                      // 1 / L[li][li] (0 for a dropped column)
+  auto step = [&](auto kc) {
+    constexpr int k = decltype(kc)::value;
+    constexpr int N0 = k < 15 ? 15 - k : 0;                  // columns k + 1 .. 15
+    constexpr int C1 = k < 15 ? 16 : k + 1;                  // columns C1 .. 31
+    const float piv = lane_of(row[k], k);
+    const bool ok = piv > thr;
+    const float root = sqrtf(ok ? piv : 1.0f), inv = 1.0f / root;
+    const float rdk = ok ? inv : 0.0f;
+    rdl = (li == k) ? rdk : rdl;
+    const float lk = (li > k) ? row[k] * rdk : 0.0f;         // L[li][k], 0 on and above the diagonal
+    row[k] = -lk;
+    if constexpr (N0 > 0) fmac_bcast<k + 1, N0>(row + k + 1, first_row(row[k]), lk);
+    if constexpr (C1 < P) fmac_bcast<C1 - 16, P - C1>(row + C1, row[k], lk);
+  };
+  [&]<int... ks>(std::integer_sequence<int, ks...>) {
+    (step(std::integral_constant<int, ks>{}), ...);
+  }(std::make_integer_sequence<int, P>{});
+  // X = L^-1, lane c column c (columns from 16 on have zeros in rows below 16,
+  // whatever the second row's lanes broadcast there)
   float x[P];
+  auto fwd = [&](auto kc) {
+    constexpr int k = decltype(kc)::value;
+    if constexpr (k == 16) {
 #pragma unroll
-  for (int k = 0; k < P; ++k) {
-    float acc = (k == lane) ? 1.0f : 0.0f;
-#pragma unroll
-    for (int m = 0; m < k; ++m)
-      acc -= __int_as_float(__builtin_amdgcn_readlane(__float_as_int(row[m]), k)) * x[m];
-    x[k] = acc * rd[k];
-  }
+      for (int m = 0; m < P; ++m) row[m] = second_row(row[m]);
+    }
+    float acc = (k == li) ? 1.0f : 0.0f;
+    dot_bcast<k % 16, k>(acc, row, x);
+    x[k] = acc * lane_of(rdl, k);
+  };
+  [&]<int... ks>(std::integer_sequence<int, ks...>) {
+    (fwd(std::integral_constant<int, ks>{}), ...);
+  }(std::make_integer_sequence<int, P>{});
   if (lane < P) {
 #pragma unroll
     for (int k = 0; k < P; ++k) Lm[lane * (P + 1) + k] = x[k] * rnl;
   }
 }
 
-// LDS carve-out of the statistics pool (16-byte aligned pieces); KF32: the
-// staged keys are fp32.
-template <int D, int P, int LB, bool KF32>
+// LDS carve-out of the statistics pool (16-byte aligned pieces); S32: the keys
+// are staged in fp32.  The staged keys are read until the Gram matrix is formed;
+// the power iteration's buffers then take their place (KEEP, subspace factors:
+// they stay behind them, projected, for the factors).  Jacobi's buffers take Y's
+// place, the Ritz vectors H's and the factors W's, each after the last reads.
+template <int D, int P, int LB, bool S32, bool KEEP>
 struct StatsLds {
   static constexpr int KS = LB + 4;                        // row stride of the transposed keys
-  static constexpr int XR = (P == 16) ? 4 : kMaxRank;      // factors the pool holds
+  static constexpr int XR = kMaxRank;                      // factors the pool holds
   static constexpr size_t al(size_t x) { return (x + 15) / 16 * 16; }
-  static constexpr size_t kt = 0;                          // raw keys, KT[e][i]
-  static constexpr size_t mean = al(kt + (size_t)D * KS * (KF32 ? 4 : 2));
+  static constexpr size_t mx(size_t a, size_t b) { return a > b ? a : b; }
+  static constexpr size_t mean = 0;
   static constexpr size_t vmean = al(mean + 4 * D);        // mean value (value-mean records)
-  static constexpr size_t sums = al(vmean + 4 * D);        // fp64 column sums per wave [4][D]
-  static constexpr size_t wm = al(sums + 8 * 4 * D);
-  static constexpr size_t ym = al(wm + 4 * LB * P);
-  static constexpr size_t sm = al(ym + 4 * LB * P);
-  static constexpr size_t lm = al(sm + 4 * P * (P + 1));
-  static constexpr size_t hm = al(lm + 4 * P * (P + 1));   // [2][P(P+1)]
-  static constexpr size_t vm = al(hm + 8 * P * (P + 1));   // [2][P(P+1)]
-  static constexpr size_t xi = al(vm + 8 * P * (P + 1));   // [XR][D] factors
-  static constexpr size_t jac = al(xi + 4 * XR * D);       // Jacobi rotations per wave: partner, c, s
+  static constexpr size_t jac = al(vmean + 4 * D);         // Jacobi rotations per wave: partner, c, s
   static constexpr size_t order = al(jac + 4 * 12 * P);
   static constexpr size_t ritz = al(order + 4 * kMaxRank);
   static constexpr size_t skw = al(ritz + 4 * kMaxRank);   // skew coefficients
   static constexpr size_t diag = al(skw + 4 * kMaxRank);   // the waves' parts of trace(Gamma)
-  static constexpr size_t bytes = al(diag + 4 * 4);
+  static constexpr size_t early = al(diag + 4 * 4);
+  static constexpr size_t sums = early;                    // fp64 column sums per wave [4][D]
+  static constexpr size_t kt = early;                      // raw keys, KT[e][i]
+  static constexpr size_t kt_end = al(kt + (size_t)D * KS * (S32 ? 4 : 2));
+  static constexpr size_t wm = KEEP ? kt_end : early;
+  static constexpr size_t sm = al(wm + 4 * LB * P);
+  static constexpr size_t ym = al(sm + 4 * P * (P + 1));
+  static constexpr size_t lm = al(ym + 4 * LB * P);
+  static constexpr size_t lm_end = al(lm + 4 * P * (P + 1));
+  static constexpr size_t hm = ym;                         // [2][P(P+1)]
+  static constexpr size_t rv = hm;                         // [XR][LB] Ritz vectors
+  static constexpr size_t vm = al(mx(hm + 8 * P * (P + 1), rv + 4 * XR * LB));   // [2][P(P+1)]
+  static constexpr size_t vm_end = al(vm + 8 * P * (P + 1));
+  static constexpr size_t xi = wm;                         // [XR][D] factors
+  static_assert(xi + 4 * XR * D <= ym, "room for the factors in W and S");
+  static constexpr size_t bytes = mx(mx(kt_end, al(sums + 8 * 4 * D)), mx(lm_end, vm_end));
 };
 
-template <int D, int P, int LB, bool KF32>
-constexpr size_t stats_lds_bytes() { return StatsLds<D, P, LB, KF32>::bytes; }
+template <int D, int P, int LB, bool KF32, bool SS>
+constexpr size_t stats_lds_bytes() { return StatsLds<D, P, LB, KF32 || SS, SS>::bytes; }
 
 // Run by a workgroup of NT >= kBuildThreads threads; the work is laid out on
 // the first kBuildThreads (four waves), every thread takes part in the barriers.
 // KF32: fp32 keys.  SS: subspace factors (Sec. 5.4), the eigen-decomposition of
 // B_b = U_Q^T Sigma_b U_Q through the Gram trick on the projected centred keys
-// Kc U_Q, staged in fp32 (the LDS pool of stats_lds_bytes<D, P, LB, true>).
+// Kc U_Q, staged in fp32.
 template <int D, int P, int LB, bool KF32, bool SS = false, int NT = kBuildThreads>
 __device__ __forceinline__ void block_stats(const StatsArgs& p, int b, int h, int j, int n, char* pool) {
   static_assert(NT % 64 == 0 && NT >= kBuildThreads, "whole waves, at least four");
   static_assert(LB == 32 || LB == 64 || LB == 128, "block of 32, 64 or 128 tokens");
   constexpr bool S32 = KF32 || SS;                 // fp32 staging
-  using Lay = StatsLds<D, P, LB, S32>;
+  using Lay = StatsLds<D, P, LB, S32, SS>;
   constexpr int KS = Lay::KS;
   constexpr int NT16 = LB / 16;                    // 16-row tiles of the block
   constexpr int RTW = (NT16 + 3) / 4;              // row tiles per wave
@@ -345,25 +373,27 @@ __device__ __forceinline__ void block_stats(const StatsArgs& p, int b, int h, in
   constexpr int NPASS = LB / RPP;
   static_assert(NPASS >= 1 && LB % RPP == 0, "whole passes");
   const int e0 = (tid % TPR) * 8, r0 = tid / TPR;
+  // elements e .. e + 7 of the row at offset `off` (negative: no row, zeros)
+  auto load8 = [&](const void* base, int64_t off, int e, float* x) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) x[q] = 0.0f;
+    if (off >= 0) {
+      if constexpr (KF32) {
+        const float4* src = reinterpret_cast<const float4*>(static_cast<const float*>(base) + off + e);
+        const float4 a = src[0], c = src[1];
+        x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = c.x; x[5] = c.y; x[6] = c.z; x[7] = c.w;
+      } else {
+        const uint4 a = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(base) + off + e);
+        x[0] = bf16_lo(a.x); x[1] = bf16_hi(a.x); x[2] = bf16_lo(a.y); x[3] = bf16_hi(a.y);
+        x[4] = bf16_lo(a.z); x[5] = bf16_hi(a.z); x[6] = bf16_lo(a.w); x[7] = bf16_hi(a.w);
+      }
+    }
+  };
   auto load_rows = [&](const void* base, float (*v)[8]) {
 #pragma unroll
     for (int ps = 0; ps < NPASS; ++ps) {
       const int i = r0 + ps * RPP;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) v[ps][q] = 0.0f;
-      const int64_t off = (lw && i < n) ? kv_offset(p.kv, b, h, j * LB + i) : -1;
-      if (off >= 0) {
-        if constexpr (KF32) {
-          const float4* src = reinterpret_cast<const float4*>(static_cast<const float*>(base) + off + e0);
-          const float4 a = src[0], c = src[1];
-          v[ps][0] = a.x; v[ps][1] = a.y; v[ps][2] = a.z; v[ps][3] = a.w;
-          v[ps][4] = c.x; v[ps][5] = c.y; v[ps][6] = c.z; v[ps][7] = c.w;
-        } else {
-          const uint4 a = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(base) + off + e0);
-          v[ps][0] = bf16_lo(a.x); v[ps][1] = bf16_hi(a.x); v[ps][2] = bf16_lo(a.y); v[ps][3] = bf16_hi(a.y);
-          v[ps][4] = bf16_lo(a.z); v[ps][5] = bf16_hi(a.z); v[ps][6] = bf16_lo(a.w); v[ps][7] = bf16_hi(a.w);
-        }
-      }
+      load8(base, (lw && i < n) ? kv_offset(p.kv, b, h, j * LB + i) : -1, e0, v[ps]);
     }
   };
   // column means: fp64 sums of the rows in registers (exact for the block's
@@ -480,6 +510,7 @@ __device__ __forceinline__ void block_stats(const StatsArgs& p, int b, int h, in
     }
     diag = wave_sum(diag);
     if (lw && lane == 0) diag_s[wave] = diag;
+    if constexpr (!SS) __syncthreads();             // the last reads of the staged keys
     for (int idx = tid; idx < LB * P; idx += NT) Wm[idx] = init_sign(idx / P, idx % P);
     __syncthreads();
     // The products use Gamma / trace(Gamma), eigenvalues in [0, 1], so that the
@@ -489,27 +520,47 @@ __device__ __forceinline__ void block_stats(const StatsArgs& p, int b, int h, in
     const float gsc = trace > 0.0f ? 1.0f / trace : 0.0f;
     // dst = (Gamma / trace) src: output row tile t of the wave, contraction in
     // steps of four indices 16a + 4 lk + v (lk = 0..3) for each (a, v)
+    // (the operands of one a, for all row tiles and columns, load together and
+    // one a ahead of their products)
     auto gamma_times = [&](const float* src, float* dst) {
+      f32x4_t acc[RTW][P / 16];
+#pragma unroll
+      for (int k = 0; k < RTW; ++k)
+#pragma unroll
+        for (int ct = 0; ct < P / 16; ++ct) acc[k][ct] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+      float bnext[4][P / 16], bcur[4][P / 16];
+      auto load_b = [&](int a) {
+#pragma unroll
+        for (int vv = 0; vv < 4; ++vv)
+#pragma unroll
+          for (int ct = 0; ct < P / 16; ++ct) bnext[vv][ct] = src[(16 * a + 4 * lk + vv) * P + 16 * ct + lr];
+      };
+      load_b(0);
+#pragma unroll
+      for (int a = 0; a < NT16; ++a) {
+#pragma unroll
+        for (int vv = 0; vv < 4; ++vv)
+#pragma unroll
+          for (int ct = 0; ct < P / 16; ++ct) bcur[vv][ct] = bnext[vv][ct];
+        if (a + 1 < NT16) load_b(a + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int vv = 0; vv < 4; ++vv)
+#pragma unroll
+          for (int k = 0; k < RTW; ++k)
+#pragma unroll
+            for (int ct = 0; ct < P / 16; ++ct)
+              acc[k][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(gr[k][a][vv], bcur[vv][ct], acc[k][ct], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
       for (int k = 0; k < RTW; ++k) {
         const int t = wave + 4 * k;
         if (lw && t < NT16) {
-          f32x4_t acc[P / 16];
-#pragma unroll
-          for (int ct = 0; ct < P / 16; ++ct) acc[ct] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-          for (int a = 0; a < NT16; ++a)
-#pragma unroll
-            for (int vv = 0; vv < 4; ++vv) {
-              const int kk = 16 * a + 4 * lk + vv;
-#pragma unroll
-              for (int ct = 0; ct < P / 16; ++ct)
-                acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(gr[k][a][vv], src[kk * P + 16 * ct + lr], acc[ct], 0, 0, 0);
-            }
 #pragma unroll
           for (int ct = 0; ct < P / 16; ++ct)
 #pragma unroll
-            for (int vv = 0; vv < 4; ++vv) dst[(16 * t + 4 * lk + vv) * P + 16 * ct + lr] = acc[ct][vv] * gsc;
+            for (int vv = 0; vv < 4; ++vv) dst[(16 * t + 4 * lk + vv) * P + 16 * ct + lr] = acc[k][ct][vv] * gsc;
         }
       }
       __syncthreads();
@@ -642,25 +693,54 @@ __device__ __forceinline__ void block_stats(const StatsArgs& p, int b, int h, in
       if (rank < r) { order[rank] = tid; ritzval[rank] = ta; }
     }
     __syncthreads();
-    // Ritz vectors w_i = W V[:, order_i] (into Y), xi_i = Kc^T w_i / sqrt(n)
+    // Ritz vectors w_i = W V[:, order_i] (in H's place), xi_i = Kc^T w_i / sqrt(n)
+    float* Rv = reinterpret_cast<float*>(pool + Lay::rv);
     for (int idx = tid; idx < r * LB; idx += NT) {
       const int i = idx / LB, row = idx % LB;
       const int col = order[i];
       float s = 0.0f;
       for (int a = 0; a < P; ++a) s += Wp[row * P + a] * Vm[cur][a * (P + 1) + col];
-      Yp[i * LB + row] = s;
+      Rv[i * LB + row] = s;
     }
     __syncthreads();
     const float rs = 1.0f / sqrtf((float)n);
     const float top = ritzval[0];
-    for (int idx = tid; idx < r * D; idx += NT) {
-      const int i = idx / D, e = idx % D;
-      float s = 0.0f;
-      if (e < fdim && ritzval[i] > 1e-6f * top && top > 0.0f) {
-        for (int row = 0; row < LB; ++row) s += kc(e, row) * Yp[i * LB + row];
-        s *= rs;
+    if constexpr (SS) {
+      for (int idx = tid; idx < r * D; idx += NT) {
+        const int i = idx / D, e = idx % D;
+        float s = 0.0f;
+        if (e < fdim && ritzval[i] > 1e-6f * top && top > 0.0f) {
+          for (int row = 0; row < LB; ++row) s += kc(e, row) * Rv[i * LB + row];
+          s *= rs;
+        }
+        Xi[i * D + e] = s;
       }
-      Xi[i * D + e] = s;
+    } else {
+      // thread t takes column e = t % D of every (256 / D)-th factor and reads
+      // that column of the keys again (L2), sixteen rows' loads in flight
+      const int e = tid % D;
+      const int64_t kb = kv_offset(p.kv, b, h, j * LB);      // a page holds one block
+      const int64_t off = (kb < 0 ? 0 : kb) + e;
+      const int64_t st = p.kv.table ? (int64_t)p.kv.d : p.kv.st;
+      const uint32_t kmask = kb < 0 ? 0u : ~0u;              // a page outside the pool: zero keys
+      const float me = mean[e];
+#pragma unroll 1
+      for (int i = tid / D; i < r; i += kBuildThreads / D) {
+        float s = 0.0f;
+#pragma unroll 1
+        for (int r0 = 0; r0 < LB; r0 += 16) {
+          float kk[16];
+#pragma unroll
+          for (int rr = 0; rr < 16; ++rr) {
+            const int64_t o = off + (r0 + rr) * st;
+            if constexpr (KF32) kk[rr] = __uint_as_float(static_cast<const uint32_t*>(p.kv.k)[o] & kmask);
+            else kk[rr] = __uint_as_float(((uint32_t)static_cast<const uint16_t*>(p.kv.k)[o] << 16) & kmask);
+          }
+#pragma unroll
+          for (int rr = 0; rr < 16; ++rr) s += (kk[rr] - me) * Rv[i * LB + r0 + rr];
+        }
+        Xi[i * D + e] = (ritzval[i] > 1e-6f * top && top > 0.0f) ? s * rs : 0.0f;
+      }
     }
     __syncthreads();
     // ---- sign: largest-magnitude entry positive (lowest index on ties); 16 threads per vector
@@ -698,7 +778,17 @@ __device__ __forceinline__ void block_stats(const StatsArgs& p, int b, int h, in
         float z3 = 0.0f;
         for (int t = lane; t < LB; t += 64) {
           float pr = 0.0f;
-          for (int e = 0; e < fdim; ++e) pr += kc(e, t) * Xi[i * D + e];
+          if constexpr (SS) {
+            for (int e = 0; e < fdim; ++e) pr += kc(e, t) * Xi[i * D + e];
+          } else {
+            const int64_t off = kv_offset(p.kv, b, h, j * LB + t);
+            for (int e8 = 0; e8 < D; e8 += 8) {
+              float kk[8];
+              load8(p.kv.k, off, e8, kk);
+#pragma unroll
+              for (int e = 0; e < 8; ++e) pr += (kk[e] - mean[e8 + e]) * Xi[i * D + e8 + e];
+            }
+          }
           const float z = (lam > 0.0f) ? pr / lam : 0.0f;
           z3 += z * z * z;
         }

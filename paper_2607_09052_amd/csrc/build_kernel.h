@@ -1,7 +1,8 @@
 // The block statistics build kernels, per (batch row, KV head, block) of LB
 // tokens: one 64-thread wave per block (block_stats_wave: L = 32 or 64, r <= 4,
 // full-space or subspace factors) or one 256-thread workgroup per block
-// (block_stats: the other configurations).
+// (block_stats on 32 columns: r > 4, or L = 128, where the 128 x 128 Gram matrix
+// of unstructured keys has a flat top).
 #pragma once
 
 #include "block_stats.h"
@@ -10,9 +11,19 @@
 
 namespace cobs {
 
-template <int D, int P, int LB, bool KF32, bool SS>
-__global__ __launch_bounds__(kBuildThreads) void build_stats_kernel(BuildParams p) {
-  constexpr size_t kPool = stats_lds_bytes<D, P, LB, KF32 || SS>();
+constexpr int kWgColumns = 32;           // power-iteration columns of the four-wave routine
+
+// Workgroups per CU (waves per SIMD) that the registers are fitted to, by the
+// LDS that a block takes.
+template <int D, int LB, bool KF32, bool SS>
+constexpr int wg_build_waves() {
+  if (SS) return 1;
+  return (KF32 && D == 128 && LB == 128) ? 2 : 3;
+}
+
+template <int D, int LB, bool KF32, bool SS, int P = kWgColumns>
+__global__ __launch_bounds__(kBuildThreads, (wg_build_waves<D, LB, KF32, SS>())) void build_stats_kernel(BuildParams p) {
+  constexpr size_t kPool = stats_lds_bytes<D, P, LB, KF32, SS>();
   constexpr size_t kProj = SS ? sizeof(float) * kProjectLdsFloats : 0;
   __shared__ __align__(16) char pool[kPool > kProj ? kPool : kProj];
   const int b = blockIdx.z, h = blockIdx.y;
@@ -130,26 +141,22 @@ hipError_t launch_build_wave(const BuildParams& p, dim3 grid, hipStream_t st) {
 }
 
 // Launch over `grid` for the block length of p.kv.
-template <int D, int P, bool SS>
-hipError_t launch_build_dp(const BuildParams& p, dim3 grid, hipStream_t st) {
+template <int D, bool SS>
+hipError_t launch_build_wg(const BuildParams& p, dim3 grid, hipStream_t st) {
   switch (p.kv.lsh) {
     case 5:
-      if (p.kv_f32) hipLaunchKernelGGL((build_stats_kernel<D, P, 32, true, SS>), grid, dim3(kBuildThreads), 0, st, p);
-      else hipLaunchKernelGGL((build_stats_kernel<D, P, 32, false, SS>), grid, dim3(kBuildThreads), 0, st, p);
+      if (p.kv_f32) hipLaunchKernelGGL((build_stats_kernel<D, 32, true, SS>), grid, dim3(kBuildThreads), 0, st, p);
+      else hipLaunchKernelGGL((build_stats_kernel<D, 32, false, SS>), grid, dim3(kBuildThreads), 0, st, p);
       break;
     case 7:
-      if (p.kv_f32) hipLaunchKernelGGL((build_stats_kernel<D, P, 128, true, SS>), grid, dim3(kBuildThreads), 0, st, p);
-      else hipLaunchKernelGGL((build_stats_kernel<D, P, 128, false, SS>), grid, dim3(kBuildThreads), 0, st, p);
+      if (p.kv_f32) hipLaunchKernelGGL((build_stats_kernel<D, 128, true, SS>), grid, dim3(kBuildThreads), 0, st, p);
+      else hipLaunchKernelGGL((build_stats_kernel<D, 128, false, SS>), grid, dim3(kBuildThreads), 0, st, p);
       break;
     default:
-      if (p.kv_f32) hipLaunchKernelGGL((build_stats_kernel<D, P, 64, true, SS>), grid, dim3(kBuildThreads), 0, st, p);
-      else hipLaunchKernelGGL((build_stats_kernel<D, P, 64, false, SS>), grid, dim3(kBuildThreads), 0, st, p);
+      if (p.kv_f32) hipLaunchKernelGGL((build_stats_kernel<D, 64, true, SS>), grid, dim3(kBuildThreads), 0, st, p);
+      else hipLaunchKernelGGL((build_stats_kernel<D, 64, false, SS>), grid, dim3(kBuildThreads), 0, st, p);
   }
   return hipGetLastError();
 }
-
-// 16 columns converge for r <= 4 at L <= 64; 32 beyond r = 4, and at L = 128,
-// where the 128 x 128 Gram matrix of unstructured keys has a flat top.
-inline bool build_big_basis(const BuildParams& p) { return p.r > 4 || p.kv.lsh == 7; }
 
 }  // namespace cobs

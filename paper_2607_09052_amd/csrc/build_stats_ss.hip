@@ -16,9 +16,7 @@ hipError_t launch_build_ss(const BuildParams& p, int d, dim3 grid, hipStream_t s
     if (p.fd == 64 && d == 128) return launch_build_wave_ss_f64(p, d, grid, st);
     if (p.fd == 96 && d == 128) return launch_build_wave_ss_f96(p, d, grid, st);
   }
-  const bool big = build_big_basis(p);
-  if (d == 128) return big ? launch_build_dp<128, 32, true>(p, grid, st) : launch_build_dp<128, 16, true>(p, grid, st);
-  return big ? launch_build_dp<64, 32, true>(p, grid, st) : launch_build_dp<64, 16, true>(p, grid, st);
+  return d == 128 ? launch_build_wg<128, true>(p, grid, st) : launch_build_wg<64, true>(p, grid, st);
 }
 
 }  // namespace cobs
