@@ -297,8 +297,8 @@ struct StatsLds {
   static constexpr size_t mx(size_t a, size_t b) { return a > b ? a : b; }
   static constexpr size_t mean = 0;
   static constexpr size_t vmean = al(mean + 4 * D);        // mean value (value-mean records)
-  static constexpr size_t jac = al(vmean + 4 * D);         // Jacobi rotations per wave: partner, c, s
-  static constexpr size_t order = al(jac + 4 * 12 * P);
+  static constexpr size_t jac = al(vmean + 4 * D);         // Jacobi rotations per wave
+  static constexpr size_t order = al(jac + 16 * 4 * P);
   static constexpr size_t ritz = al(order + 4 * kMaxRank);
   static constexpr size_t skw = al(ritz + 4 * kMaxRank);   // skew coefficients
   static constexpr size_t diag = al(skw + 4 * kMaxRank);   // the waves' parts of trace(Gamma)
@@ -309,8 +309,8 @@ struct StatsLds {
   static constexpr size_t wm = KEEP ? kt_end : early;
   static constexpr size_t sm = al(wm + 4 * LB * P);
   static constexpr size_t ym = al(sm + 4 * P * (P + 1));
-  static constexpr size_t lm = al(ym + 4 * LB * P);
-  static constexpr size_t lm_end = al(lm + 4 * P * (P + 1));
+  static constexpr size_t lm = sm;                         // N X^T (S is read whole before it is written)
+  static constexpr size_t lm_end = al(ym + 4 * LB * P);
   static constexpr size_t hm = ym;                         // [2][P(P+1)]
   static constexpr size_t rv = hm;                         // [XR][LB] Ritz vectors
   static constexpr size_t vm = al(mx(hm + 8 * P * (P + 1), rv + 4 * XR * LB));   // [2][P(P+1)]
@@ -349,7 +349,6 @@ __device__ __forceinline__ void block_stats(const StatsArgs& p, int b, int h, in
   float (*Hm)[P * (P + 1)] = reinterpret_cast<float (*)[P * (P + 1)]>(pool + Lay::hm);
   float (*Vm)[P * (P + 1)] = reinterpret_cast<float (*)[P * (P + 1)]>(pool + Lay::vm);
   float* Xi = reinterpret_cast<float*>(pool + Lay::xi);
-  int* partner = reinterpret_cast<int*>(pool + Lay::jac);        // [4 waves][partner, c, s][P]
   int* order = reinterpret_cast<int*>(pool + Lay::order);
   float* ritzval = reinterpret_cast<float*>(pool + Lay::ritz);
   float* skw = reinterpret_cast<float*>(pool + Lay::skw);
@@ -635,50 +634,59 @@ __device__ __forceinline__ void block_stats(const StatsArgs& p, int b, int h, in
     static_assert(NT == kBuildThreads, "one rotation slot per wave of the work layout");
     int cw = 0;
     {
-      int* partner_w = partner + (tid >> 6) * 3 * P;
-      float* cself_w = reinterpret_cast<float*>(partner_w + P);
-      float* cpart_w = reinterpret_cast<float*>(partner_w + 2 * P);
+      // rotation of index x: its partner, own and partner's coefficient (one
+      // 16-byte word, per wave)
+      int4* rot_w = reinterpret_cast<int4*>(pool + Lay::jac) + (tid >> 6) * P;
       for (int sweep = 0; sweep < kJacobiSweeps; ++sweep) {
-        bool moved = false;
+        uint64_t moved = 0;
         for (int rnd = 0; rnd < P - 1; ++rnd) {
           bool big = false;
           if (lw && lane < P / 2) {
-            const int m1 = lane, m2 = P - 1 - lane;
-            const int x = (m1 == 0) ? 0 : 1 + (m1 - 1 + rnd) % (P - 1);
-            const int y = 1 + (m2 - 1 + rnd) % (P - 1);
+            // slots lane and P - 1 - lane of the round
+            int x = lane - 1 + rnd, y = P - 2 - lane + rnd;
+            x = (lane == 0) ? 0 : 1 + (x >= P - 1 ? x - (P - 1) : x);
+            y = 1 + (y >= P - 1 ? y - (P - 1) : y);
             const int pp = min(x, y), qq = max(x, y);
             const float* H = Hm[cw];
             const float app = H[pp * (P + 1) + pp], aqq = H[qq * (P + 1) + qq], apq = H[pp * (P + 1) + qq];
             float c = 1.0f, s = 0.0f;
-            big = fabsf(apq) > 1e-6f * sqrtf(fmaxf(app, 0.0f) * fmaxf(aqq, 0.0f)) && fabsf(apq) > 2e-8f;
+            big = fabsf(apq) > fmaxf(1e-6f * __builtin_amdgcn_sqrtf(fmaxf(app, 0.0f) * fmaxf(aqq, 0.0f)), 2e-8f);
             if (apq != 0.0f) {
               const float th = (aqq - app) / (2.0f * apq);
               const float t = (th >= 0.0f ? 1.0f : -1.0f) / (fabsf(th) + sqrtf(th * th + 1.0f));
               c = 1.0f / sqrtf(t * t + 1.0f);
               s = t * c;
             }
-            partner_w[pp] = qq; partner_w[qq] = pp;
-            cself_w[pp] = c; cpart_w[pp] = -s;
-            cself_w[qq] = c; cpart_w[qq] = s;
+            rot_w[pp] = make_int4(qq, __float_as_int(c), __float_as_int(-s), 0);
+            rot_w[qq] = make_int4(pp, __float_as_int(c), __float_as_int(s), 0);
           }
-          moved = moved || __ballot(big) != 0;
+          moved |= __ballot(big);
           wave_lds_sync();
           const float* H = Hm[cw];
           const float* V = Vm[cw];
           float* H2 = Hm[cw ^ 1];
           float* V2 = Vm[cw ^ 1];
-          for (int idx = tid; lw && idx < P * P; idx += kBuildThreads) {
-            const int a = idx / P, c = idx % P;
-            const int pa = partner_w[a], pc = partner_w[c];
-            const float sa = cself_w[a], ta = cpart_w[a], sc = cself_w[c], tc = cpart_w[c];
-            H2[a * (P + 1) + c] = sa * sc * H[a * (P + 1) + c] + sa * tc * H[a * (P + 1) + pc] +
-                                  ta * sc * H[pa * (P + 1) + c] + ta * tc * H[pa * (P + 1) + pc];
-            V2[a * (P + 1) + c] = V[a * (P + 1) + c] * sc + V[a * (P + 1) + pc] * tc;
+          if (lw) {
+            // column c of this thread, rows a, a + 8, ..
+            const int c = tid % P;
+            const int4 rc = rot_w[c];
+            const int pc = rc.x;
+            const float sc = __int_as_float(rc.y), tc = __int_as_float(rc.z);
+#pragma unroll
+            for (int q = 0; q < P * P / kBuildThreads; ++q) {
+              const int a = tid / P + q * (kBuildThreads / P);
+              const int4 ra = rot_w[a];
+              const int pa = ra.x;
+              const float sa = __int_as_float(ra.y), ta = __int_as_float(ra.z);
+              H2[a * (P + 1) + c] = sa * sc * H[a * (P + 1) + c] + sa * tc * H[a * (P + 1) + pc] +
+                                    ta * sc * H[pa * (P + 1) + c] + ta * tc * H[pa * (P + 1) + pc];
+              V2[a * (P + 1) + c] = V[a * (P + 1) + c] * sc + V[a * (P + 1) + pc] * tc;
+            }
           }
           __syncthreads();
           cw ^= 1;
         }
-        if (!moved) break;
+        if (moved == 0) break;
       }
     }
     const int cur = cw;                  // the buffer the last round wrote
@@ -782,6 +790,7 @@ __device__ __forceinline__ void block_stats(const StatsArgs& p, int b, int h, in
             for (int e = 0; e < fdim; ++e) pr += kc(e, t) * Xi[i * D + e];
           } else {
             const int64_t off = kv_offset(p.kv, b, h, j * LB + t);
+#pragma unroll 1
             for (int e8 = 0; e8 < D; e8 += 8) {
               float kk[8];
               load8(p.kv.k, off, e8, kk);

@@ -267,22 +267,18 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
 #pragma unroll
         for (int e = 0; e < FPR; ++e) cs[e] += (double)feature(kw[v], e);
     };
-    if (whole) {
 #pragma unroll
-      for (int a0 = 0; a0 < NT16; a0 += QB) {
-        uint32_t kw[QB][4][ZW];
+    for (int a0 = 0; a0 < NT16; a0 += QB) {
+      uint32_t kw[QB][4][ZW];
+      if (whole) {
 #pragma unroll
         for (int a = 0; a < QB; ++a) load_rows4(base, a0 + a, kw[a]);
+      } else {
 #pragma unroll
-        for (int a = 0; a < QB; ++a) add(kw[a]);
+        for (int a = 0; a < QB; ++a) load_rows4_masked(base, a0 + a, kw[a]);
       }
-    } else {
-#pragma unroll 1
-      for (int a = 0; a < NT16; ++a) {
-        uint32_t kw[4][ZW];
-        load_rows4_masked(base, a, kw);
-        add(kw);
-      }
+#pragma unroll
+      for (int a = 0; a < QB; ++a) add(kw[a]);
     }
 #pragma unroll
     for (int e = 0; e < FPR; ++e) cs[e] = row_groups_sum(cs[e]);

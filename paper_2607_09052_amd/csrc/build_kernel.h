@@ -14,15 +14,25 @@ namespace cobs {
 constexpr int kWgColumns = 32;           // power-iteration columns of the four-wave routine
 
 // Workgroups per CU (waves per SIMD) that the registers are fitted to, by the
-// LDS that a block takes.
+// LDS that a block takes.  A block's serial parts (Cholesky on one wave, Jacobi's
+// rounds) leave the CU to the others: 2,048 blocks of 128 tokens (d = 128,
+// r = 4, bf16 keys) take 1,320 us with four (128 registers, 192 spilled, mostly
+// the Gram matrix across the Cholesky), 1,436 with three, and took 3,534 with
+// one, which 107 KB of LDS allowed.
 template <int D, int LB, bool KF32, bool SS>
 constexpr int wg_build_waves() {
   if (SS) return 1;
-  return (KF32 && D == 128 && LB == 128) ? 2 : 3;
+  if (LB == 128) return !KF32 ? 4 : (D == 128 ? 2 : 3);
+  return 3;
 }
 
-template <int D, int LB, bool KF32, bool SS, int P = kWgColumns>
-__global__ __launch_bounds__(kBuildThreads, (wg_build_waves<D, LB, KF32, SS>())) void build_stats_kernel(BuildParams p) {
+// With no more blocks than CUs each workgroup has a CU to itself, and nothing
+// is gained by fewer registers: the decode step's build of four newest blocks of
+// 128 tokens costs the step 5 us more on the four-to-a-CU form than on this one.
+constexpr int64_t kCus = 256;
+
+template <int D, int LB, bool KF32, bool SS, int WAVES, int P = kWgColumns>
+__global__ __launch_bounds__(kBuildThreads, WAVES) void build_stats_kernel(BuildParams p) {
   constexpr size_t kPool = stats_lds_bytes<D, P, LB, KF32, SS>();
   constexpr size_t kProj = SS ? sizeof(float) * kProjectLdsFloats : 0;
   __shared__ __align__(16) char pool[kPool > kProj ? kPool : kProj];
@@ -140,21 +150,30 @@ hipError_t launch_build_wave(const BuildParams& p, dim3 grid, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int D, int LB, bool KF32, bool SS>
+void launch_build_wg_as(const BuildParams& p, dim3 grid, hipStream_t st) {
+  if ((int64_t)grid.x * grid.y * grid.z <= kCus)
+    hipLaunchKernelGGL((build_stats_kernel<D, LB, KF32, SS, 1>), grid, dim3(kBuildThreads), 0, st, p);
+  else
+    hipLaunchKernelGGL((build_stats_kernel<D, LB, KF32, SS, wg_build_waves<D, LB, KF32, SS>()>), grid,
+                       dim3(kBuildThreads), 0, st, p);
+}
+
 // Launch over `grid` for the block length of p.kv.
 template <int D, bool SS>
 hipError_t launch_build_wg(const BuildParams& p, dim3 grid, hipStream_t st) {
   switch (p.kv.lsh) {
     case 5:
-      if (p.kv_f32) hipLaunchKernelGGL((build_stats_kernel<D, 32, true, SS>), grid, dim3(kBuildThreads), 0, st, p);
-      else hipLaunchKernelGGL((build_stats_kernel<D, 32, false, SS>), grid, dim3(kBuildThreads), 0, st, p);
+      if (p.kv_f32) launch_build_wg_as<D, 32, true, SS>(p, grid, st);
+      else launch_build_wg_as<D, 32, false, SS>(p, grid, st);
       break;
     case 7:
-      if (p.kv_f32) hipLaunchKernelGGL((build_stats_kernel<D, 128, true, SS>), grid, dim3(kBuildThreads), 0, st, p);
-      else hipLaunchKernelGGL((build_stats_kernel<D, 128, false, SS>), grid, dim3(kBuildThreads), 0, st, p);
+      if (p.kv_f32) launch_build_wg_as<D, 128, true, SS>(p, grid, st);
+      else launch_build_wg_as<D, 128, false, SS>(p, grid, st);
       break;
     default:
-      if (p.kv_f32) hipLaunchKernelGGL((build_stats_kernel<D, 64, true, SS>), grid, dim3(kBuildThreads), 0, st, p);
-      else hipLaunchKernelGGL((build_stats_kernel<D, 64, false, SS>), grid, dim3(kBuildThreads), 0, st, p);
+      if (p.kv_f32) launch_build_wg_as<D, 64, true, SS>(p, grid, st);
+      else launch_build_wg_as<D, 64, false, SS>(p, grid, st);
   }
   return hipGetLastError();
 }

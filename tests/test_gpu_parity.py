@@ -563,9 +563,8 @@ def test_build_stats_matches_oracle(law, d, r, L):
 
 
 def _spectrum_keys(law, L, d, seed):
-    """Keys whose covariance has a given shape: the step plan of the one-wave
-    solver follows the spectrum (few steps for a clear gap, the most for a flat
-    one, the plain ones when columns of its basis drop out)."""
+    """Keys whose covariance has a given shape: a clear gap or none behind the
+    factors, a plateau, and a rank below the basis (columns that drop out)."""
     rng = np.random.default_rng(seed)
     s = {"decay0.2": 0.2 ** (np.arange(d) / 2.0), "decay0.5": 0.5 ** (np.arange(d) / 2.0),
          "decay0.8": 0.8 ** (np.arange(d) / 2.0), "flat": np.ones(d),
@@ -590,6 +589,31 @@ def test_build_stats_over_spectra(law, d, r, L):
     _, _, factors = R.decode(rec[0, 0].cpu().numpy(), d, r, "f32", "f32")
     for blk in range(nblk):
         ky_fan_checks(factors[blk], K[blk * L:blk * L + L].astype(np.float64), L, r)
+
+
+@pytest.mark.parametrize("d,r,L,kv", [(128, 4, 128, "bf16"), (64, 2, 128, "bf16"), (128, 3, 128, "f32"), (128, 6, 64, "bf16"),
+                                      (64, 16, 32, "f32")])
+def test_build_of_few_and_of_many_blocks_is_the_same(d, r, L, kv):
+    """The four-wave routine is built for one workgroup per CU (launches of up to
+    256 blocks) and for several: the records are the same bytes."""
+    nblk = 257
+    T = nblk * L - 5                                     # the newest block is partial
+    k, v = (torch.randn(1, 1, nblk * L, d, generator=torch.Generator().manual_seed(d + r + L + i)) for i in (0, 1))
+    dt = torch.bfloat16 if kv == "bf16" else torch.float32
+    k, v = k.to(DEV, dt), v.to(DEV, dt)
+    cfg = _cfg(batch=1, num_q_heads=1, num_kv_heads=1, head_dim=d, max_seq_len=nblk * L, rank=r, kv_dtype=kv,
+               block_size=L, value_mean=True)
+    seq = torch.tensor([T], dtype=torch.int32, device=DEV)
+    say(f"build of {nblk} blocks and of 256 and 1: d={d} r={r} L={L} {kv}")
+    many, few = cobs.new_summaries(cfg, DEV), cobs.new_summaries(cfg, DEV)
+    cobs.cobs_build_block_stats(cfg, k, v, seq, many)
+    cobs.cobs_build_block_stats(cfg, k, v, seq, few, first_block=0, num_blocks=256)
+    cobs.cobs_build_block_stats(cfg, k, v, seq, few, first_block=256, num_blocks=1)
+    sync()
+    assert torch.equal(many, few)
+    factors = R.decode(many[0, 0].cpu().numpy(), d, r, "f32", "f32", value_mean=True)[2]
+    for blk in (0, 255):
+        ky_fan_checks(factors[blk], k[0, 0, blk * L:(blk + 1) * L].double().cpu().numpy(), L, r)
 
 
 def test_build_bf16_keys_and_storage_dtypes_consistent():
