@@ -103,6 +103,29 @@ class Config:
     # U_Q of every KV head for subspace factors: fp32 [Hkv, d, subspace_dim] on the GPU
     query_basis: object = dataclasses.field(default=None, compare=False, repr=False)
 
+    def __setattr__(self, name, value):
+        object.__setattr__(self, name, value)
+        self.__dict__["_state"] = object()             # after the field: see marshalled
+
+    def __getstate__(self):                            # copies and pickles hold the fields alone
+        return {k: v for k, v in self.__dict__.items() if k not in ("_state", "_marshalled")}
+
+    def marshalled(self):
+        """The C form of the fields: (struct, record bytes, K/V torch dtype or None).
+        Made once per change of a field: it is filed under the `_state` read before
+        the fields, which every assignment replaces after its field is set, so what a
+        thread made while another one assigned is never used again.  With a query
+        basis, whose tensor may change under it, it is made anew for each call."""
+        state = self.__dict__.get("_state")
+        m = self.__dict__.get("_marshalled")
+        if m is not None and state is not None and m[3] is state:
+            return m[:3]
+        c = self.c_struct()
+        m = (c, int(lib().cobs_record_bytes(ctypes.byref(c))), _TORCH_DTYPE.get(self.kv_dtype), state)
+        if self.query_basis is None:
+            self.__dict__["_marshalled"] = m
+        return m[:3]
+
     @property
     def options(self):
         return (OPT_SKEW if self.skew else 0) | (OPT_VALUE_MEAN if self.value_mean else 0)
@@ -130,13 +153,18 @@ class Config:
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(stream, dev_tensor):
     if stream is not None:
-        return ctypes.c_void_p(stream if isinstance(stream, int) else stream.cuda_stream)
-    return ctypes.c_void_p(torch.cuda.current_stream(dev_tensor.device).cuda_stream)
+        return stream if isinstance(stream, int) else stream.cuda_stream
+    if _raw_stream is not None:
+        return _raw_stream(dev_tensor.get_device())
+    return torch.cuda.current_stream(dev_tensor.device).cuda_stream
 
 
 def _check(status):
@@ -180,6 +208,32 @@ def _same_gpu(**tensors):
             raise CobsError(f"{name} is on {t.device}, the call runs on {dev}")
 
 
+# Every entry point looks its arguments over in one pass (_fits, _kv_fits); only
+# when something does not fit does it run the checks one by one (_need, _kv,
+# _same_gpu), which name the fault, or find that there is none.  A small decode
+# step is bound by the calling thread, and the separate checks were most of it.
+
+def _fits(dev, *checks):
+    """Every (tensor or None, dtype, elements) contiguous on GPU `dev`, and large enough."""
+    for t, dtype, n in checks:
+        if t is not None and not (t.dtype is dtype and t.numel() >= n and t.get_device() == dev and t.is_contiguous()):
+            return False
+    return dev >= 0
+
+
+def _kv_fits(cfg, dtype, dev, k, v):
+    """The C view of a contiguous-mode cache on GPU `dev`, or None if anything does not fit."""
+    if k.dtype is not dtype or v.dtype is not dtype:
+        return None
+    shape, stride = k.shape, k.stride()
+    if len(shape) != 4 or v.shape != shape or v.stride() != stride or k.get_device() != dev or v.get_device() != dev:
+        return None
+    if (shape[3] != cfg.head_dim or stride[3] != 1 or shape[0] < cfg.batch or shape[1] < cfg.num_kv_heads or
+            shape[2] < cfg.max_seq_len):
+        return None
+    return _KV(k.data_ptr(), v.data_ptr(), stride[0], stride[1], stride[2], None, 0)
+
+
 def _kv(cfg, k, v, block_table=None, num_pages=0):
     """Validated K/V view (contiguous [>=B, >=Hkv, >=T_max, d] with the head
     dimension dense, or pages [num_pages, Hkv, L, d] with a [B, T_max/L] table)."""
@@ -219,7 +273,7 @@ def _ws(ws):
 
 
 def _summaries(cfg, summaries):
-    return _need("summaries", summaries, torch.uint8, _units(cfg) * cfg.num_blocks * record_bytes(cfg))
+    return _need("summaries", summaries, torch.uint8, _units(cfg) * cfg.num_blocks * cfg.marshalled()[1])
 
 
 def record_bytes(cfg):
@@ -245,12 +299,20 @@ def cobs_build_block_stats(cfg, k, v, seq_lens, summaries, first_block=0, num_bl
                            ws=None, block_table=None, num_pages=0, stream=None):
     if num_blocks is None:
         num_blocks = cfg.num_blocks - first_block
-    _need("seq_lens", seq_lens, torch.int32, cfg.batch)
-    _summaries(cfg, summaries)
-    kv = _kv(cfg, k, v, block_table, num_pages)
-    _same_gpu(seq_lens=seq_lens, summaries=summaries, k=k, v=v, block_table=block_table,
-              query_basis=cfg.query_basis)
-    _check(lib().cobs_build_block_stats(ctypes.byref(cfg.c_struct()), ctypes.byref(kv),
+    c, rb, kvt = cfg.marshalled()
+    kv = None
+    if (seq_lens is not None and summaries is not None and k is not None and v is not None and
+            block_table is None and cfg.query_basis is None):
+        dev = summaries.get_device()
+        if _fits(dev, (seq_lens, torch.int32, cfg.batch), (summaries, torch.uint8, _units(cfg) * cfg.num_blocks * rb)):
+            kv = _kv_fits(cfg, kvt, dev, k, v)
+    if kv is None:
+        _need("seq_lens", seq_lens, torch.int32, cfg.batch)
+        _summaries(cfg, summaries)
+        kv = _kv(cfg, k, v, block_table, num_pages)
+        _same_gpu(seq_lens=seq_lens, summaries=summaries, k=k, v=v, block_table=block_table,
+                  query_basis=cfg.query_basis)
+    _check(lib().cobs_build_block_stats(ctypes.byref(c), ctypes.byref(kv),
                                         _ptr(seq_lens), int(first_block), int(num_blocks),
                                         _ptr(summaries), _ptr(ws),
                                         0 if ws is None else ws.numel() * ws.element_size(),
@@ -317,29 +379,54 @@ def cobs_sparse_decode(cfg, q, k, v, seq_lens, sel, out, ws, lse=None, block_tab
                                     _stream(stream, q)))
 
 
+def _attend_fits(cfg, q, k, v, seq_lens, sel, outs, lses, ws, block_table, summaries=None):
+    """The C view of the cache if every argument of an attention call fits, else None."""
+    if (q is None or seq_lens is None or ws is None or k is None or v is None or block_table is not None or
+            cfg.query_basis is not None or any(o is None for o in outs)):
+        return None
+    dev, nq = q.get_device(), cfg.batch * cfg.num_q_heads
+    _, rb, kvt = cfg.marshalled()
+    if not _fits(dev, (q, torch.float32, nq * cfg.head_dim), (seq_lens, torch.int32, cfg.batch),
+                 (sel, torch.int32, _units(cfg) * cfg.budget), (ws, ws.dtype, 0),
+                 (summaries, torch.uint8, _units(cfg) * cfg.num_blocks * rb),
+                 *((o, torch.float32, nq * cfg.head_dim) for o in outs), *((l, torch.float32, nq) for l in lses)):
+        return None
+    return _kv_fits(cfg, kvt, dev, k, v)
+
+
 def cobs_sparse_decode_branches(cfg, q, k, v, seq_lens, sel, out_sel, out_win, ws, lse_sel=None, lse_win=None,
                                 block_table=None, num_pages=0, stream=None):
-    _decode_io(cfg, q, seq_lens, sel, dict(out_sel=out_sel, out_win=out_win), dict(lse_sel=lse_sel, lse_win=lse_win))
-    kv = _kv(cfg, k, v, block_table, num_pages)
-    nws = _ws(ws)
-    _same_gpu(q=q, k=k, v=v, seq_lens=seq_lens, sel=sel, out_sel=out_sel, out_win=out_win, lse_sel=lse_sel,
-              lse_win=lse_win, ws=ws, block_table=block_table)
-    _check(lib().cobs_sparse_decode_branches(ctypes.byref(cfg.c_struct()), _ptr(q), ctypes.byref(kv),
+    kv = None
+    if sel is not None:
+        kv = _attend_fits(cfg, q, k, v, seq_lens, sel, (out_sel, out_win), (lse_sel, lse_win), ws, block_table)
+    if kv is None:
+        _decode_io(cfg, q, seq_lens, sel, dict(out_sel=out_sel, out_win=out_win),
+                   dict(lse_sel=lse_sel, lse_win=lse_win))
+        kv = _kv(cfg, k, v, block_table, num_pages)
+        _ws(ws)
+        _same_gpu(q=q, k=k, v=v, seq_lens=seq_lens, sel=sel, out_sel=out_sel, out_win=out_win, lse_sel=lse_sel,
+                  lse_win=lse_win, ws=ws, block_table=block_table)
+    _check(lib().cobs_sparse_decode_branches(ctypes.byref(cfg.marshalled()[0]), _ptr(q), ctypes.byref(kv),
                                              _ptr(seq_lens), _ptr(sel), _ptr(out_sel), _ptr(lse_sel),
-                                             _ptr(out_win), _ptr(lse_win), _ptr(ws), nws, _stream(stream, q)))
+                                             _ptr(out_win), _ptr(lse_win), _ptr(ws),
+                                             ws.numel() * ws.element_size(), _stream(stream, q)))
 
 
 def cobs_decode_step(cfg, q, k, v, seq_lens, summaries, out, ws, sel=None, lse=None,
                      block_table=None, num_pages=0, stream=None):
-    _decode_io(cfg, q, seq_lens, sel, dict(out=out), dict(lse=lse), sel_required=False)
-    _summaries(cfg, summaries)
-    kv = _kv(cfg, k, v, block_table, num_pages)
-    nws = _ws(ws)
-    _same_gpu(q=q, k=k, v=v, seq_lens=seq_lens, summaries=summaries, sel=sel, out=out, lse=lse, ws=ws,
-              block_table=block_table, query_basis=cfg.query_basis)
-    _check(lib().cobs_decode_step(ctypes.byref(cfg.c_struct()), _ptr(q), ctypes.byref(kv),
+    kv = None
+    if summaries is not None:
+        kv = _attend_fits(cfg, q, k, v, seq_lens, sel, (out,), (lse,), ws, block_table, summaries)
+    if kv is None:
+        _decode_io(cfg, q, seq_lens, sel, dict(out=out), dict(lse=lse), sel_required=False)
+        _summaries(cfg, summaries)
+        kv = _kv(cfg, k, v, block_table, num_pages)
+        _ws(ws)
+        _same_gpu(q=q, k=k, v=v, seq_lens=seq_lens, summaries=summaries, sel=sel, out=out, lse=lse, ws=ws,
+                  block_table=block_table, query_basis=cfg.query_basis)
+    _check(lib().cobs_decode_step(ctypes.byref(cfg.marshalled()[0]), _ptr(q), ctypes.byref(kv),
                                   _ptr(seq_lens), _ptr(summaries), _ptr(sel), _ptr(out), _ptr(lse),
-                                  _ptr(ws), nws, _stream(stream, q)))
+                                  _ptr(ws), ws.numel() * ws.element_size(), _stream(stream, q)))
 
 
 def cobs_decode_step_noalloc(cfg, q, k, v, seq_lens, summaries, out, sel=None, lse=None,
@@ -357,13 +444,19 @@ def cobs_decode_step_noalloc(cfg, q, k, v, seq_lens, summaries, out, sel=None, l
 
 def cobs_compression_branch(cfg, q, summaries, seq_lens, out, lse=None, stream=None):
     """The mean-pool compression branch over value-mean records (cfg.value_mean)."""
-    _need("q", q, torch.float32, cfg.batch * cfg.num_q_heads * cfg.head_dim)
-    _need("seq_lens", seq_lens, torch.int32, cfg.batch)
-    _summaries(cfg, summaries)
-    _need("out", out, torch.float32, cfg.batch * cfg.num_q_heads * cfg.head_dim)
-    _opt("lse", lse, torch.float32, cfg.batch * cfg.num_q_heads)
-    _same_gpu(q=q, summaries=summaries, seq_lens=seq_lens, out=out, lse=lse)
-    _check(lib().cobs_compression_branch(ctypes.byref(cfg.c_struct()), _ptr(q), _ptr(summaries), _ptr(seq_lens),
+    c, rb, _ = cfg.marshalled()
+    nq = cfg.batch * cfg.num_q_heads
+    if (q is None or summaries is None or seq_lens is None or out is None or
+            not _fits(q.get_device(), (q, torch.float32, nq * cfg.head_dim), (seq_lens, torch.int32, cfg.batch),
+                      (summaries, torch.uint8, _units(cfg) * cfg.num_blocks * rb),
+                      (out, torch.float32, nq * cfg.head_dim), (lse, torch.float32, nq))):
+        _need("q", q, torch.float32, nq * cfg.head_dim)
+        _need("seq_lens", seq_lens, torch.int32, cfg.batch)
+        _summaries(cfg, summaries)
+        _need("out", out, torch.float32, nq * cfg.head_dim)
+        _opt("lse", lse, torch.float32, nq)
+        _same_gpu(q=q, summaries=summaries, seq_lens=seq_lens, out=out, lse=lse)
+    _check(lib().cobs_compression_branch(ctypes.byref(c), _ptr(q), _ptr(summaries), _ptr(seq_lens),
                                          _ptr(out), _ptr(lse), _stream(stream, q)))
 
 

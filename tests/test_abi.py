@@ -4,11 +4,13 @@ arguments on the host before touching the GPU.  CPU only: no kernel launches.
 """
 
 import ctypes
+import dataclasses
 import os
 import re
 import subprocess
 
 import pytest
+import torch
 
 from oracle import records as R
 from paper_2607_09052_amd import cobs
@@ -254,6 +256,53 @@ def test_binding_rejects_tensors_the_kernels_would_misread():
     rejects(dec, cfg, q, k[:, :, :512], k[:, :, :512], seq, sel, out, ws, match="smaller than")
     rejects(dec, cfg, q, k, k, seq, sel, out, ws, block_table=torch.zeros((B, 16), dtype=torch.int32),
             num_pages=4, match="paged k must be")
+
+
+def test_marshalled_config_follows_its_fields():
+    import copy
+    import pickle
+    cfg = _cfg()
+    for name, value in (("batch", 3), ("rank", 2), ("mean_dtype", "bf16"), ("skew", True), ("softmax_scale", 0.5)):
+        cfg.marshalled()
+        other = copy.copy(cfg)
+        setattr(cfg, name, value)
+        for c in (cfg, other, pickle.loads(pickle.dumps(cfg)), dataclasses.replace(cfg)):
+            s, rb, kvt = c.marshalled()
+            assert bytes(s) == bytes(c.c_struct()) and rb == cobs.record_bytes(c)
+            assert kvt == cobs._TORCH_DTYPE[c.kv_dtype]
+        assert getattr(other, name) != value and getattr(other.marshalled()[0], "batch") == other.batch
+    assert dataclasses.replace(cfg) == cfg
+
+
+@pytest.mark.parametrize("form", ["plain", "larger", "transposed", "sliced_head_dim", "short", "few_heads", "small_batch",
+                                  "other_strides", "other_dtype", "other_dim", "three_dims"])
+def test_one_pass_cache_check_agrees_with_the_separate_checks(form):
+    """_kv_fits returns the view of _kv, or None for what _kv refuses."""
+    cfg = _cfg()
+    B, H, T, d = cfg.batch, cfg.num_kv_heads, cfg.max_seq_len, cfg.head_dim
+
+    def z(*shape, dtype=torch.bfloat16):
+        return torch.empty(shape, dtype=dtype)
+
+    make = {"plain": lambda: z(B, H, T, d), "larger": lambda: z(B + 1, H + 2, T + 5, d),
+            "transposed": lambda: z(B, T, H, d).transpose(1, 2), "sliced_head_dim": lambda: z(B, H, T, 2 * d)[..., ::2],
+            "short": lambda: z(B, H, T - 1, d), "few_heads": lambda: z(B, H - 1, T, d),
+            "small_batch": lambda: z(B - 1, H, T, d), "other_strides": lambda: z(B, H, T, d),
+            "other_dtype": lambda: z(B, H, T, d, dtype=torch.float32), "other_dim": lambda: z(B, H, T, d // 2),
+            "three_dims": lambda: z(H, T, d)}[form]
+    k, v = make(), make()
+    if form == "other_strides":
+        v = z(B, T, H, d).transpose(1, 2)
+    got = cobs._kv_fits(cfg, torch.bfloat16, -1, k, v)
+    if form in ("plain", "larger", "transposed"):
+        want = cobs._kv(cfg, k, v)
+        assert [getattr(got, f) for f, _ in want._fields_] == [getattr(want, f) for f, _ in want._fields_]
+        assert cobs._kv_fits(cfg, torch.bfloat16, 0, k, v) is None          # a cache on another device
+        assert not cobs._fits(-1, (k, torch.bfloat16, 1))                   # nothing fits on no GPU
+    else:
+        assert got is None
+        with pytest.raises(cobs.CobsError):
+            cobs._kv(cfg, k, v)
 
 
 def test_noalloc_step_rejects_problems_beyond_its_scratch():
