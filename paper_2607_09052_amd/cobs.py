@@ -213,6 +213,11 @@ def _same_gpu(**tensors):
 # _same_gpu), which name the fault, or find that there is none.  A small decode
 # step is bound by the calling thread, and the separate checks were most of it.
 
+def _gpu(t):
+    """Index of the tensor's GPU; -1 for anything else, which the separate checks name."""
+    return t.get_device() if isinstance(t, torch.Tensor) else -1
+
+
 def _fits(dev, *checks):
     """Every (tensor or None, dtype, elements) contiguous on GPU `dev`, and large enough."""
     for t, dtype, n in checks:
@@ -303,7 +308,7 @@ def cobs_build_block_stats(cfg, k, v, seq_lens, summaries, first_block=0, num_bl
     kv = None
     if (seq_lens is not None and summaries is not None and k is not None and v is not None and
             block_table is None and cfg.query_basis is None):
-        dev = summaries.get_device()
+        dev = _gpu(summaries)
         if _fits(dev, (seq_lens, torch.int32, cfg.batch), (summaries, torch.uint8, _units(cfg) * cfg.num_blocks * rb)):
             kv = _kv_fits(cfg, kvt, dev, k, v)
     if kv is None:
@@ -384,7 +389,7 @@ def _attend_fits(cfg, q, k, v, seq_lens, sel, outs, lses, ws, block_table, summa
     if (q is None or seq_lens is None or ws is None or k is None or v is None or block_table is not None or
             cfg.query_basis is not None or any(o is None for o in outs)):
         return None
-    dev, nq = q.get_device(), cfg.batch * cfg.num_q_heads
+    dev, nq = _gpu(q), cfg.batch * cfg.num_q_heads
     _, rb, kvt = cfg.marshalled()
     if not _fits(dev, (q, torch.float32, nq * cfg.head_dim), (seq_lens, torch.int32, cfg.batch),
                  (sel, torch.int32, _units(cfg) * cfg.budget), (ws, ws.dtype, 0),
@@ -447,7 +452,7 @@ def cobs_compression_branch(cfg, q, summaries, seq_lens, out, lse=None, stream=N
     c, rb, _ = cfg.marshalled()
     nq = cfg.batch * cfg.num_q_heads
     if (q is None or summaries is None or seq_lens is None or out is None or
-            not _fits(q.get_device(), (q, torch.float32, nq * cfg.head_dim), (seq_lens, torch.int32, cfg.batch),
+            not _fits(_gpu(q), (q, torch.float32, nq * cfg.head_dim), (seq_lens, torch.int32, cfg.batch),
                       (summaries, torch.uint8, _units(cfg) * cfg.num_blocks * rb),
                       (out, torch.float32, nq * cfg.head_dim), (lse, torch.float32, nq))):
         _need("q", q, torch.float32, nq * cfg.head_dim)

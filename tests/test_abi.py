@@ -305,6 +305,20 @@ def test_one_pass_cache_check_agrees_with_the_separate_checks(form):
             cobs._kv(cfg, k, v)
 
 
+def test_arguments_that_are_no_tensors_get_the_separate_checks_error():
+    import numpy as np
+    cfg = _cfg()
+    x = np.zeros(4, np.float32)
+    k = torch.empty((cfg.batch, cfg.num_kv_heads, cfg.max_seq_len, cfg.head_dim), dtype=torch.bfloat16)
+    seq = torch.zeros(cfg.batch, dtype=torch.int32)
+    for call in (lambda: cobs.cobs_decode_step(cfg, x, k, k, seq, seq, seq, seq),
+                 lambda: cobs.cobs_sparse_decode_branches(cfg, x, k, k, seq, seq, seq, seq, seq),
+                 lambda: cobs.cobs_compression_branch(cfg, x, seq, seq, seq),
+                 lambda: cobs.cobs_build_block_stats(cfg, k, k, seq, x)):
+        with pytest.raises(cobs.CobsError, match="must be torch"):
+            call()
+
+
 def test_noalloc_step_rejects_problems_beyond_its_scratch():
     """cobs_decode_step_noalloc refuses, on the host, a problem whose step
     workspace exceeds the library's per-GPU array."""
