@@ -26,6 +26,9 @@ namespace cobs {
 
 constexpr int kCmpThreads = 1024;
 
+// Four floats of the queries, whose address need only be that of a float.
+typedef float query4_t __attribute__((ext_vector_type(4), aligned(4)));
+
 // Blocks of a 16-lane group per pass: two where four would spill (128 registers).
 template <int D, int HW, int MDT>
 constexpr int cmp_batch() { return (D == 128 && HW == 4 && MDT != DT_BF16) ? 2 : 4; }
@@ -68,7 +71,7 @@ __global__ __launch_bounds__(kCmpThreads) void compress_kernel(CompressParams p)
     l[g] = 0.0f;
 #pragma unroll
     for (int e = 0; e < EPL; e += 4) {
-      const float4 x = *reinterpret_cast<const float4*>(p.q + (head0 + g) * D + EPL * ln + e);
+      const query4_t x = *reinterpret_cast<const query4_t*>(p.q + (head0 + g) * D + EPL * ln + e);
       q[g][e] = x.x * p.c; q[g][e + 1] = x.y * p.c; q[g][e + 2] = x.z * p.c; q[g][e + 3] = x.w * p.c;
     }
 #pragma unroll

@@ -239,3 +239,10 @@ def test_compression_branch_head_splits(d, G, md):
             for i in range(G):
                 assert rel_l2(got_o[i], o[i]) <= 1e-5, (b, h, i, rel_l2(got_o[i], o[i]))
             np.testing.assert_allclose(got_l, l, rtol=0, atol=LSE_TOL * max(1.0, float(np.max(np.abs(l)))))
+    # queries at the address of a float, as a view into a larger buffer has them
+    buf = torch.empty(q.numel() + 1, dtype=torch.float32, device=DEV)
+    buf[1:] = q.reshape(-1)
+    again = torch.empty_like(out)
+    cobs.cobs_compression_branch(cfg, buf[1:].view(q.shape), rec, seq, again)
+    sync()
+    assert torch.equal(again, out)
