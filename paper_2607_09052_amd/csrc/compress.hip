@@ -78,19 +78,33 @@ __global__ __launch_bounds__(kCmpThreads) void compress_kernel(CompressParams p)
     for (int e = 0; e < EPL; ++e) o[g][e] = 0.0f;
   }
 
-  for (int base = 4 * U * wave; base < nb; base += 4 * U * NW) {
-    // block base + 4 u + grp of pass element u; past the last block its record
-    // is read again and its score is -inf
-    uint32_t kw[U][MW], vw[U][MW];
-    float ks[U], vs[U];
+  // Block base + 4 u + grp of pass element u; past the last block its record is
+  // read again and its score is -inf.  With fp32 vectors of 128 elements and one
+  // head a pass's registers are loaded for the next one as soon as they are
+  // unpacked (the keys before the softmax, the values at the end of the pass):
+  // 4 x 8 units of 1016 blocks, two heads per KV head, take 16.2 us instead of
+  // 20.3.  Smaller vectors gain nothing (bf16, one head: 9.7 against 10.2 us
+  // ahead), and more heads leave no registers for it.
+  constexpr int kStep = 4 * U * NW;
+  constexpr bool kAhead = MDT == DT_F32 && D == 128 && HW == 1;
+  uint32_t kw[U][MW], vw[U][MW];
+  float ks[U], vs[U];
+  auto load = [&](int base, auto keys, auto values) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint8_t* R = recu + (int64_t)min(base + 4 * u + grp, nb - 1) * p.lay.total;
-      load_part<D, MDT>(R + p.lay.mean_off, ln, kw[u]);
-      load_part<D, MDT>(R + p.lay.vmean_off, ln, vw[u]);
-      ks[u] = (MDT == DT_E2M1) ? *reinterpret_cast<const float*>(R + 4) : 1.0f;
-      vs[u] = (MDT == DT_E2M1) ? *reinterpret_cast<const float*>(R + 8) : 1.0f;
+      if constexpr (keys()) load_part<D, MDT>(R + p.lay.mean_off, ln, kw[u]);
+      if constexpr (values()) load_part<D, MDT>(R + p.lay.vmean_off, ln, vw[u]);
+      if constexpr (keys()) ks[u] = (MDT == DT_E2M1) ? *reinterpret_cast<const float*>(R + 4) : 1.0f;
+      if constexpr (values()) vs[u] = (MDT == DT_E2M1) ? *reinterpret_cast<const float*>(R + 8) : 1.0f;
     }
+  };
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
+  if (kAhead && 4 * U * wave < nb) load(4 * U * wave, yes, yes);
+  for (int base = 4 * U * wave; base < nb; base += kStep) {
+    const bool more = kAhead && base + kStep < nb;
+    if constexpr (!kAhead) load(base, yes, yes);
     float sc[U][HW];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -106,6 +120,7 @@ __global__ __launch_bounds__(kCmpThreads) void compress_kernel(CompressParams p)
         sc[u][g] = live ? a : -INFINITY;
       }
     }
+    if (more) load(base + kStep, yes, no);
 #pragma unroll
     for (int g = 0; g < HW; ++g) {
       float mn = m[g];
@@ -135,6 +150,7 @@ __global__ __launch_bounds__(kCmpThreads) void compress_kernel(CompressParams p)
         for (int e = 0; e < EPL; ++e) o[g][e] += pr * x[e];
       }
     }
+    if (more) load(base + kStep, no, yes);
   }
   // ---- the four groups' states of the wave
 #pragma unroll

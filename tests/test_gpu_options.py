@@ -206,9 +206,10 @@ def test_compression_branch_matches_oracle(d, G, kv, md):
 
 # head splits of the branch's workgroups: 64 units of 16 heads take four heads
 # each, of 8 heads two, of 4 heads one; block counts around the pass of 256
-# (16 waves of 16 blocks; 128 for four heads of fp32 and E2M1 means at d = 128)
+# (16 waves of 16 blocks; 128 for four heads of fp32 and E2M1 means at d = 128);
+# one head of fp32 vectors at d = 128 loads a pass ahead
 @pytest.mark.parametrize("d,G,md", [(128, 16, "f32"), (128, 16, "bf16"), (128, 16, "e2m1"), (128, 8, "bf16"),
-                                    (64, 16, "e2m1"), (64, 8, "f32"), (64, 4, "bf16")])
+                                    (64, 16, "e2m1"), (64, 8, "f32"), (64, 4, "bf16"), (128, 2, "f32")])
 def test_compression_branch_head_splits(d, G, md):
     T, B, Hkv, L = 32 * 300, 8, 8, 32
     g = torch.Generator(device=DEV)
