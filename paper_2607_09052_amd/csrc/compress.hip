@@ -17,7 +17,7 @@
 // group in one workgroup, its CU's vector ALUs (2 G D multiply-adds per block).
 // So the heads are split over workgroups until the chip is covered (see
 // launch_compress); the workgroups of one unit read the same records, the
-// later ones from L2.  10.7 us a call at that case (4 heads per KV head, bf16
+// later ones from L2.  10.5 us a call at that case (4 heads per KV head, bf16
 // means; one 256-thread workgroup per unit, whose value pass loaded one block
 // at a time, took 47.4).
 #include "select_impl.h"
@@ -79,12 +79,14 @@ __global__ __launch_bounds__(kCmpThreads) void compress_kernel(CompressParams p)
   }
 
   // Block base + 4 u + grp of pass element u; past the last block its record is
-  // read again and its score is -inf.  With fp32 vectors of 128 elements and one
-  // head a pass's registers are loaded for the next one as soon as they are
-  // unpacked (the keys before the softmax, the values at the end of the pass):
-  // 4 x 8 units of 1016 blocks, two heads per KV head, take 16.2 us instead of
-  // 20.3.  Smaller vectors gain nothing (bf16, one head: 9.7 against 10.2 us
-  // ahead), and more heads leave no registers for it.
+  // read again, its score is -inf and its value words are cleared (probability 0
+  // times an infinite value would be NaN).  Only a wave's last pass can hold such
+  // elements: the others are compiled without the tests.
+  // With fp32 vectors of 128 elements and one head a pass's registers are loaded
+  // for the next one as soon as they are unpacked (the keys before the softmax,
+  // the values at the end of the pass): 4 x 8 units of 1016 blocks, two heads per
+  // KV head, take 16.6 us instead of 20.3.  Smaller vectors gain nothing (bf16,
+  // one head: 9.8 against 10.2 us ahead), and more heads leave no registers for it.
   constexpr int kStep = 4 * U * NW;
   constexpr bool kAhead = MDT == DT_F32 && D == 128 && HW == 1;
   uint32_t kw[U][MW], vw[U][MW];
@@ -102,13 +104,13 @@ __global__ __launch_bounds__(kCmpThreads) void compress_kernel(CompressParams p)
   constexpr std::true_type yes{};
   constexpr std::false_type no{};
   if (kAhead && 4 * U * wave < nb) load(4 * U * wave, yes, yes);
-  for (int base = 4 * U * wave; base < nb; base += kStep) {
+  auto pass = [&](int base, auto whole) {
     const bool more = kAhead && base + kStep < nb;
     if constexpr (!kAhead) load(base, yes, yes);
     float sc[U][HW];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const bool live = base + 4 * u + grp < nb;
+      const bool live = whole() || base + 4 * u + grp < nb;
       float x[EPL];
       unpack_elems<MDT, EPL>(kw[u], x);
 #pragma unroll
@@ -139,6 +141,15 @@ __global__ __launch_bounds__(kCmpThreads) void compress_kernel(CompressParams p)
         l[g] += sc[u][g];
       }
     }
+    if (!whole() && base + 4 * U > nb) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool live = base + 4 * u + grp < nb;
+#pragma unroll
+        for (int w = 0; w < MW; ++w) vw[u][w] = live ? vw[u][w] : 0u;
+        vs[u] = live ? vs[u] : 0.0f;
+      }
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       float x[EPL];
@@ -151,6 +162,13 @@ __global__ __launch_bounds__(kCmpThreads) void compress_kernel(CompressParams p)
       }
     }
     if (more) load(base + kStep, no, yes);
+  };
+  int base = 4 * U * wave;
+  if constexpr (kAhead) {                // (two forms of the pass would spill)
+    for (; base < nb; base += kStep) pass(base, no);
+  } else {
+    for (; base + 4 * U <= nb; base += kStep) pass(base, yes);
+    if (base < nb) pass(base, no);
   }
   // ---- the four groups' states of the wave
 #pragma unroll

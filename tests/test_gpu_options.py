@@ -247,3 +247,42 @@ def test_compression_branch_head_splits(d, G, md):
     cobs.cobs_compression_branch(cfg, buf[1:].view(q.shape), rec, seq, again)
     sync()
     assert torch.equal(again, out)
+
+
+# an infinite element in the newest block's mean value, at block counts that leave
+# elements of the last pass (16 blocks of a wave, or 8) without a block
+@pytest.mark.parametrize("d,G,md,B,Hkv", [(128, 1, "f32", 4, 2), (128, 4, "bf16", 4, 2), (64, 4, "f32", 4, 2),
+                                          (64, 2, "bf16", 4, 2), (128, 16, "f32", 8, 8), (128, 8, "bf16", 8, 8)])
+def test_compression_branch_with_infinite_values(d, G, md, B, Hkv):
+    L, counts = 32, [1, 15, 257, 130, 16, 9, 2, 250][:B]
+    T = L * max(counts)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(800 + G + d)
+    k, v = (torch.randn(B, Hkv, T, d, generator=g, device=DEV).to(torch.bfloat16) for _ in range(2))
+    q = torch.randn(B, G * Hkv, d, generator=g, device=DEV)
+    for b, n in enumerate(counts):
+        v[b, :, L * n - 1, 5] = float("inf")
+        v[b, :, L * n - 2, d - 1] = float("-inf")
+    cfg = _cfg(d, 0, "bf16", md, "bf16", T, G=G, B=B, Hkv=Hkv, value_mean=True, block_size=L)
+    seq = torch.tensor([L * n for n in counts], dtype=torch.int32, device=DEV)
+    rec = cobs.new_summaries(cfg, DEV)
+    say(f"compression branch with infinite values d={d} G={G} mean {md}")
+    cobs.cobs_build_block_stats(cfg, k, v, seq, rec)
+    out = torch.full((B, G * Hkv, d), 7.0, dtype=torch.float32, device=DEV)
+    lse = torch.full((B, G * Hkv), 7.0, dtype=torch.float32, device=DEV)
+    cobs.cobs_compression_branch(cfg, q, rec, seq, out, lse)
+    sync()
+    for b, n in enumerate(counts):
+        for h in (0, Hkv - 1):
+            gs = slice(h * G, (h + 1) * G)
+            got = out[b, gs].cpu().numpy()
+            cnt, mns, _, vmn = (R.decode(rec[b, h, :n].cpu().numpy(), d, 0, md, "bf16", False, True)[i]
+                                for i in (0, 1, 2, -1))
+            o, l = M.compression_attention(f64(q[b, gs]), cnt, mns, vmn, cfg.scale)
+            assert np.all(np.isposinf(got[:, 5])) and np.all(np.isneginf(got[:, d - 1])), (b, h)
+            assert np.all(np.isposinf(o[:, 5])) and np.all(np.isneginf(o[:, d - 1]))
+            for i in range(G):
+                fin = np.isfinite(o[i])
+                assert fin.sum() == d - 2 and rel_l2(got[i][fin], o[i][fin]) <= 1e-5, (b, h, i)
+            np.testing.assert_allclose(lse[b, gs].cpu().numpy(), l, rtol=0,
+                                       atol=LSE_TOL * max(1.0, float(np.max(np.abs(l)))))
