@@ -10,6 +10,7 @@ there is no other implementation to fall back to.
 import ctypes
 import dataclasses
 import math
+import operator
 import os
 
 import torch
@@ -81,8 +82,14 @@ def lib():
     return _lib
 
 
+class _CForm:
+    """The place of a Config's C form (Config.marshalled): outside its __dict__, so
+    that vars(), comparisons, copies and pickles see the fields alone."""
+    __slots__ = ("_c_form",)
+
+
 @dataclasses.dataclass
-class Config:
+class Config(_CForm):
     """Problem description (cobs_config_t)."""
     batch: int
     num_q_heads: int
@@ -103,28 +110,26 @@ class Config:
     # U_Q of every KV head for subspace factors: fp32 [Hkv, d, subspace_dim] on the GPU
     query_basis: object = dataclasses.field(default=None, compare=False, repr=False)
 
-    def __setattr__(self, name, value):
-        object.__setattr__(self, name, value)
-        self.__dict__["_state"] = object()             # after the field: see marshalled
-
-    def __getstate__(self):                            # copies and pickles hold the fields alone
-        return {k: v for k, v in self.__dict__.items() if k not in ("_state", "_marshalled")}
+    def __getstate__(self):
+        return self.__dict__
 
     def marshalled(self):
         """The C form of the fields: (struct, record bytes, K/V torch dtype or None).
-        Made once per change of a field: it is filed under the `_state` read before
-        the fields, which every assignment replaces after its field is set, so what a
-        thread made while another one assigned is never used again.  With a query
-        basis, whose tensor may change under it, it is made anew for each call."""
-        state = self.__dict__.get("_state")
-        m = self.__dict__.get("_marshalled")
-        if m is not None and state is not None and m[3] is state:
-            return m[:3]
-        c = self.c_struct()
-        m = (c, int(lib().cobs_record_bytes(ctypes.byref(c))), _TORCH_DTYPE.get(self.kv_dtype), state)
-        if self.query_basis is None:
-            self.__dict__["_marshalled"] = m
-        return m[:3]
+        It is kept with the values that it was made from and used again while every
+        field is the same object, however it may have been set.  Only plain numbers
+        and texts are compared so: with anything that can change in place (a query
+        basis, an array) it is made anew for each call."""
+        kept = getattr(self, "_c_form", None)
+        fields = _config_fields(self)
+        if kept is not None and all(map(operator.is_, fields, kept[0])):
+            return kept[1]
+        plain = type(self) is Config and fields[-1] is None and all(type(x) in _PLAIN for x in fields[:-1])
+        src = Config(*fields) if plain else self       # the values read, if another thread sets one meanwhile
+        c = src.c_struct()
+        form = (c, int(lib().cobs_record_bytes(ctypes.byref(c))), _TORCH_DTYPE.get(src.kv_dtype))
+        if plain:
+            self._c_form = (fields, form)
+        return form
 
     @property
     def options(self):
@@ -150,6 +155,10 @@ class Config:
     @property
     def scale(self):
         return self.softmax_scale if self.softmax_scale > 0 else 1.0 / math.sqrt(self.head_dim)
+
+
+_config_fields = operator.attrgetter(*(f.name for f in dataclasses.fields(Config)))    # query_basis is the last
+_PLAIN = (int, float, bool, str)
 
 
 def _ptr(t):
@@ -277,8 +286,8 @@ def _ws(ws):
     return ws.numel() * ws.element_size()
 
 
-def _summaries(cfg, summaries):
-    return _need("summaries", summaries, torch.uint8, _units(cfg) * cfg.num_blocks * cfg.marshalled()[1])
+def _summaries(cfg, summaries, rec_bytes):
+    return _need("summaries", summaries, torch.uint8, _units(cfg) * cfg.num_blocks * rec_bytes)
 
 
 def record_bytes(cfg):
@@ -313,7 +322,7 @@ def cobs_build_block_stats(cfg, k, v, seq_lens, summaries, first_block=0, num_bl
             kv = _kv_fits(cfg, kvt, dev, k, v)
     if kv is None:
         _need("seq_lens", seq_lens, torch.int32, cfg.batch)
-        _summaries(cfg, summaries)
+        _summaries(cfg, summaries, rb)
         kv = _kv(cfg, k, v, block_table, num_pages)
         _same_gpu(seq_lens=seq_lens, summaries=summaries, k=k, v=v, block_table=block_table,
                   query_basis=cfg.query_basis)
@@ -333,11 +342,12 @@ def _select_io(cfg, q, seq_lens, sel, scores):
 
 def cobs_select(cfg, q, summaries, seq_lens, sel, ws, scores=None, stream=None):
     _select_io(cfg, q, seq_lens, sel, scores)
-    _summaries(cfg, summaries)
+    c, rb, _ = cfg.marshalled()
+    _summaries(cfg, summaries, rb)
     nws = _ws(ws)
     _same_gpu(q=q, summaries=summaries, seq_lens=seq_lens, sel=sel, scores=scores, ws=ws,
               query_basis=cfg.query_basis)
-    _check(lib().cobs_select(ctypes.byref(cfg.c_struct()), _ptr(q), _ptr(summaries),
+    _check(lib().cobs_select(ctypes.byref(c), _ptr(q), _ptr(summaries),
                              _ptr(seq_lens), _ptr(sel), _ptr(scores), _ptr(ws), nws, _stream(stream, q)))
 
 
@@ -384,26 +394,27 @@ def cobs_sparse_decode(cfg, q, k, v, seq_lens, sel, out, ws, lse=None, block_tab
                                     _stream(stream, q)))
 
 
-def _attend_fits(cfg, q, k, v, seq_lens, sel, outs, lses, ws, block_table, summaries=None):
+def _attend_fits(cfg, rec_bytes, kv_dtype, q, k, v, seq_lens, sel, outs, lses, ws, block_table, summaries=None):
     """The C view of the cache if every argument of an attention call fits, else None."""
     if (q is None or seq_lens is None or ws is None or k is None or v is None or block_table is not None or
             cfg.query_basis is not None or any(o is None for o in outs)):
         return None
     dev, nq = _gpu(q), cfg.batch * cfg.num_q_heads
-    _, rb, kvt = cfg.marshalled()
     if not _fits(dev, (q, torch.float32, nq * cfg.head_dim), (seq_lens, torch.int32, cfg.batch),
                  (sel, torch.int32, _units(cfg) * cfg.budget), (ws, ws.dtype, 0),
-                 (summaries, torch.uint8, _units(cfg) * cfg.num_blocks * rb),
+                 (summaries, torch.uint8, _units(cfg) * cfg.num_blocks * rec_bytes),
                  *((o, torch.float32, nq * cfg.head_dim) for o in outs), *((l, torch.float32, nq) for l in lses)):
         return None
-    return _kv_fits(cfg, kvt, dev, k, v)
+    return _kv_fits(cfg, kv_dtype, dev, k, v)
 
 
 def cobs_sparse_decode_branches(cfg, q, k, v, seq_lens, sel, out_sel, out_win, ws, lse_sel=None, lse_win=None,
                                 block_table=None, num_pages=0, stream=None):
+    c, rb, kvt = cfg.marshalled()
     kv = None
     if sel is not None:
-        kv = _attend_fits(cfg, q, k, v, seq_lens, sel, (out_sel, out_win), (lse_sel, lse_win), ws, block_table)
+        kv = _attend_fits(cfg, rb, kvt, q, k, v, seq_lens, sel, (out_sel, out_win), (lse_sel, lse_win), ws,
+                          block_table)
     if kv is None:
         _decode_io(cfg, q, seq_lens, sel, dict(out_sel=out_sel, out_win=out_win),
                    dict(lse_sel=lse_sel, lse_win=lse_win))
@@ -411,7 +422,7 @@ def cobs_sparse_decode_branches(cfg, q, k, v, seq_lens, sel, out_sel, out_win, w
         _ws(ws)
         _same_gpu(q=q, k=k, v=v, seq_lens=seq_lens, sel=sel, out_sel=out_sel, out_win=out_win, lse_sel=lse_sel,
                   lse_win=lse_win, ws=ws, block_table=block_table)
-    _check(lib().cobs_sparse_decode_branches(ctypes.byref(cfg.marshalled()[0]), _ptr(q), ctypes.byref(kv),
+    _check(lib().cobs_sparse_decode_branches(ctypes.byref(c), _ptr(q), ctypes.byref(kv),
                                              _ptr(seq_lens), _ptr(sel), _ptr(out_sel), _ptr(lse_sel),
                                              _ptr(out_win), _ptr(lse_win), _ptr(ws),
                                              ws.numel() * ws.element_size(), _stream(stream, q)))
@@ -419,17 +430,18 @@ def cobs_sparse_decode_branches(cfg, q, k, v, seq_lens, sel, out_sel, out_win, w
 
 def cobs_decode_step(cfg, q, k, v, seq_lens, summaries, out, ws, sel=None, lse=None,
                      block_table=None, num_pages=0, stream=None):
+    c, rb, kvt = cfg.marshalled()
     kv = None
     if summaries is not None:
-        kv = _attend_fits(cfg, q, k, v, seq_lens, sel, (out,), (lse,), ws, block_table, summaries)
+        kv = _attend_fits(cfg, rb, kvt, q, k, v, seq_lens, sel, (out,), (lse,), ws, block_table, summaries)
     if kv is None:
         _decode_io(cfg, q, seq_lens, sel, dict(out=out), dict(lse=lse), sel_required=False)
-        _summaries(cfg, summaries)
+        _summaries(cfg, summaries, rb)
         kv = _kv(cfg, k, v, block_table, num_pages)
         _ws(ws)
         _same_gpu(q=q, k=k, v=v, seq_lens=seq_lens, summaries=summaries, sel=sel, out=out, lse=lse, ws=ws,
                   block_table=block_table, query_basis=cfg.query_basis)
-    _check(lib().cobs_decode_step(ctypes.byref(cfg.marshalled()[0]), _ptr(q), ctypes.byref(kv),
+    _check(lib().cobs_decode_step(ctypes.byref(c), _ptr(q), ctypes.byref(kv),
                                   _ptr(seq_lens), _ptr(summaries), _ptr(sel), _ptr(out), _ptr(lse),
                                   _ptr(ws), ws.numel() * ws.element_size(), _stream(stream, q)))
 
@@ -438,11 +450,12 @@ def cobs_decode_step_noalloc(cfg, q, k, v, seq_lens, summaries, out, sel=None, l
                              block_table=None, num_pages=0, stream=None):
     """cobs_decode_step on the library's own per-GPU workspace (no ws argument)."""
     _decode_io(cfg, q, seq_lens, sel, dict(out=out), dict(lse=lse), sel_required=False)
-    _summaries(cfg, summaries)
+    c, rb, _ = cfg.marshalled()
+    _summaries(cfg, summaries, rb)
     kv = _kv(cfg, k, v, block_table, num_pages)
     _same_gpu(q=q, k=k, v=v, seq_lens=seq_lens, summaries=summaries, sel=sel, out=out, lse=lse,
               block_table=block_table, query_basis=cfg.query_basis)
-    _check(lib().cobs_decode_step_noalloc(ctypes.byref(cfg.c_struct()), _ptr(q), ctypes.byref(kv),
+    _check(lib().cobs_decode_step_noalloc(ctypes.byref(c), _ptr(q), ctypes.byref(kv),
                                           _ptr(seq_lens), _ptr(summaries), _ptr(sel), _ptr(out), _ptr(lse),
                                           _stream(stream, q)))
 
@@ -457,7 +470,7 @@ def cobs_compression_branch(cfg, q, summaries, seq_lens, out, lse=None, stream=N
                       (out, torch.float32, nq * cfg.head_dim), (lse, torch.float32, nq))):
         _need("q", q, torch.float32, nq * cfg.head_dim)
         _need("seq_lens", seq_lens, torch.int32, cfg.batch)
-        _summaries(cfg, summaries)
+        _summaries(cfg, summaries, rb)
         _need("out", out, torch.float32, nq * cfg.head_dim)
         _opt("lse", lse, torch.float32, nq)
         _same_gpu(q=q, summaries=summaries, seq_lens=seq_lens, out=out, lse=lse)

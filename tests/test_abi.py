@@ -274,6 +274,46 @@ def test_marshalled_config_follows_its_fields():
     assert dataclasses.replace(cfg) == cfg
 
 
+def test_marshalled_config_follows_fields_set_past_setattr():
+    """The fields are a Config's whole state, and its C form is the fields' however
+    they came to be what they are."""
+    import copy
+    import pickle
+
+    import numpy as np
+    cfg = _cfg()
+    cfg.marshalled()
+    names = [f.name for f in dataclasses.fields(cobs.Config)]
+    assert list(vars(cfg)) == names and cobs.Config(**vars(cfg)) == cfg
+
+    def follows(c, batch):
+        s, rb, _ = c.marshalled()
+        assert s.batch == batch and bytes(s) == bytes(c.c_struct()) and rb == cobs.record_bytes(c)
+
+    vars(cfg).update(batch=5, rank=3)
+    follows(cfg, 5)
+    object.__setattr__(cfg, "batch", 6)
+    follows(cfg, 6)
+    cfg.__dict__ = dict(reversed(vars(cfg).items()), batch=7)
+    follows(cfg, 7)
+    del cfg.softmax_scale                                   # the class's default shows
+    follows(cfg, 7)
+    cfg.softmax_scale = scale = np.full((), 0.5)            # changes in place
+    follows(cfg, 7)
+    scale[...] = 0.25
+    assert cfg.marshalled()[0].softmax_scale == 0.25
+    cfg.softmax_scale = 0.5
+    cfg.batch = 8
+    follows(cfg, 8)
+    cfg.batch = 8.0                                         # equal, but refused as before
+    with pytest.raises(TypeError):
+        cfg.marshalled()
+    cfg.batch = 8
+    for other in (copy.copy(cfg), copy.deepcopy(cfg), pickle.loads(pickle.dumps(cfg)), dataclasses.replace(cfg)):
+        assert other == cfg and set(vars(other)) == set(names)
+        assert other.marshalled() is other.marshalled()     # kept from the first use on
+
+
 @pytest.mark.parametrize("form", ["plain", "larger", "transposed", "sliced_head_dim", "short", "few_heads", "small_batch",
                                   "other_strides", "other_dtype", "other_dim", "three_dims"])
 def test_one_pass_cache_check_agrees_with_the_separate_checks(form):
