@@ -537,7 +537,8 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
     }
 
     // ---- Rayleigh-Ritz: H = W^T (Gamma W), symmetrised; V = I (the buffers from
-    // here on take the place of Gamma's parts)
+    // here on take the place of Gamma's parts, which the last product has read)
+    wave_lds_sync();
     put_mean(kmean, mean);
     small_gram(w, y, Sm);
     to_rows(w);                          // W by rows, for the Ritz vectors
