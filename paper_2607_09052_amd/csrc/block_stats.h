@@ -311,6 +311,9 @@ struct StatsLds {
   static constexpr size_t ym = al(sm + 4 * P * (P + 1));
   static constexpr size_t lm = sm;                         // N X^T (S is read whole before it is written)
   static constexpr size_t lm_end = al(ym + 4 * LB * P);
+  // H lies over Y: each double step swaps the basis' buffer with its image's, so the
+  // basis, read until the Ritz vectors are formed, ends in W's after an even number
+  static_assert((kPowerIters - kSinglePowerIters) % 2 == 0, "H would overwrite the basis");
   static constexpr size_t hm = ym;                         // [2][P(P+1)]
   static constexpr size_t rv = hm;                         // [XR][LB] Ritz vectors
   static constexpr size_t vm = al(mx(hm + 8 * P * (P + 1), rv + 4 * XR * LB));   // [2][P(P+1)]
