@@ -26,11 +26,6 @@ constexpr int wg_build_waves() {
   return 3;
 }
 
-// With no more blocks than CUs each workgroup has a CU to itself, and nothing
-// is gained by fewer registers: the decode step's build of four newest blocks of
-// 128 tokens costs the step 5 us more on the four-to-a-CU form than on this one.
-constexpr int64_t kCus = 256;
-
 template <int D, int LB, bool KF32, bool SS, int WAVES, int P = kWgColumns>
 __global__ __launch_bounds__(kBuildThreads, WAVES) void build_stats_kernel(BuildParams p) {
   constexpr size_t kPool = stats_lds_bytes<D, P, LB, KF32, SS>();
@@ -150,9 +145,12 @@ hipError_t launch_build_wave(const BuildParams& p, dim3 grid, hipStream_t st) {
   return hipGetLastError();
 }
 
+// With no more blocks than the device has CUs each workgroup has a CU to itself,
+// and nothing is gained by fewer registers: the decode step's build of four newest
+// blocks of 128 tokens costs the step 5 us more on the four-to-a-CU form.
 template <int D, int LB, bool KF32, bool SS>
 void launch_build_wg_as(const BuildParams& p, dim3 grid, hipStream_t st) {
-  if ((int64_t)grid.x * grid.y * grid.z <= kCus)
+  if ((int64_t)grid.x * grid.y * grid.z <= device_cus())
     hipLaunchKernelGGL((build_stats_kernel<D, LB, KF32, SS, 1>), grid, dim3(kBuildThreads), 0, st, p);
   else
     hipLaunchKernelGGL((build_stats_kernel<D, LB, KF32, SS, wg_build_waves<D, LB, KF32, SS>()>), grid,

@@ -595,8 +595,10 @@ def test_build_stats_over_spectra(law, d, r, L):
                                       (64, 16, 32, "f32")])
 def test_build_of_few_and_of_many_blocks_is_the_same(d, r, L, kv):
     """The four-wave routine is built for one workgroup per CU (launches of up to
-    256 blocks) and for several: the records are the same bytes."""
-    nblk = 257
+    as many blocks as the device has CUs) and for several: the records are the
+    same bytes."""
+    cus = torch.cuda.get_device_properties(DEV).multi_processor_count
+    nblk = cus + 1
     T = nblk * L - 5                                     # the newest block is partial
     k, v = (torch.randn(1, 1, nblk * L, d, generator=torch.Generator().manual_seed(d + r + L + i)) for i in (0, 1))
     dt = torch.bfloat16 if kv == "bf16" else torch.float32
@@ -604,15 +606,15 @@ def test_build_of_few_and_of_many_blocks_is_the_same(d, r, L, kv):
     cfg = _cfg(batch=1, num_q_heads=1, num_kv_heads=1, head_dim=d, max_seq_len=nblk * L, rank=r, kv_dtype=kv,
                block_size=L, value_mean=True)
     seq = torch.tensor([T], dtype=torch.int32, device=DEV)
-    say(f"build of {nblk} blocks and of 256 and 1: d={d} r={r} L={L} {kv}")
+    say(f"build of {nblk} blocks and of {cus} and 1: d={d} r={r} L={L} {kv}")
     many, few = cobs.new_summaries(cfg, DEV), cobs.new_summaries(cfg, DEV)
     cobs.cobs_build_block_stats(cfg, k, v, seq, many)
-    cobs.cobs_build_block_stats(cfg, k, v, seq, few, first_block=0, num_blocks=256)
-    cobs.cobs_build_block_stats(cfg, k, v, seq, few, first_block=256, num_blocks=1)
+    cobs.cobs_build_block_stats(cfg, k, v, seq, few, first_block=0, num_blocks=cus)
+    cobs.cobs_build_block_stats(cfg, k, v, seq, few, first_block=cus, num_blocks=1)
     sync()
     assert torch.equal(many, few)
     factors = R.decode(many[0, 0].cpu().numpy(), d, r, "f32", "f32", value_mean=True)[2]
-    for blk in (0, 255):
+    for blk in (0, cus - 1):
         ky_fan_checks(factors[blk], k[0, 0, blk * L:(blk + 1) * L].double().cpu().numpy(), L, r)
 
 
