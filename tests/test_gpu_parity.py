@@ -512,6 +512,42 @@ def test_paged_ids_outside_the_pool_read_as_zero_keys(dt):
     sync()
     assert torch.equal(rec_s, rec_p)
 
+
+# every routine that reads a block's keys again for its factors and skew
+# coefficients: one wave per block (L <= 64, r <= 4) and four, keys of both types
+@pytest.mark.parametrize("d,r,L,kv", [(128, 4, 128, "bf16"), (64, 3, 128, "f32"), (128, 6, 64, "f32"),
+                                      (64, 8, 64, "bf16"), (128, 16, 32, "bf16"), (128, 2, 32, "f32"),
+                                      (64, 4, 64, "bf16")])
+def test_build_with_pages_outside_the_pool_at_every_block_length_and_rank(d, r, L, kv):
+    """As above for the build alone, with skew coefficients and value means: full
+    and ragged blocks whose page lies outside the pool (below it, one past its
+    end, far past it) have the records of zero keys and values."""
+    B, Hkv, nbm = 2, 2, 6
+    Tmax = nbm * L
+    dt = torch.bfloat16 if kv == "bf16" else torch.float32
+    g = torch.Generator().manual_seed(17 + d + r + L)
+    k, v = ((torch.randn(B, Hkv, Tmax, d, generator=g) + 0.5).to(dt) for _ in range(2))
+    cfg = _cfg(batch=B, num_q_heads=Hkv, num_kv_heads=Hkv, head_dim=d, max_seq_len=Tmax, rank=r, kv_dtype=kv,
+               block_size=L, skew=True, value_mean=True)
+    pages = B * nbm
+    kp, vp = (x.view(B, Hkv, nbm, L, d).permute(0, 2, 1, 3, 4).reshape(pages, Hkv, L, d).contiguous().to(DEV)
+              for x in (k, v))
+    table = torch.arange(pages, dtype=torch.int32).view(B, nbm).clone()
+    for b, j, pid in ((0, 2, -1), (0, 5, pages), (1, 0, 1 << 30), (1, 3, pages + 7)):   # (1, 3): ragged
+        table[b, j] = pid
+        k[b, :, j * L:(j + 1) * L] = 0
+        v[b, :, j * L:(j + 1) * L] = 0
+    seq = torch.tensor([Tmax, 3 * L + L // 2 + 1], dtype=torch.int32, device=DEV)
+    say(f"pages outside the pool: build d={d} r={r} L={L} {kv}")
+    rec_c, rec_p = cobs.new_summaries(cfg, DEV), cobs.new_summaries(cfg, DEV)
+    cobs.cobs_build_block_stats(cfg, k.to(DEV), v.to(DEV), seq, rec_c)
+    cobs.cobs_build_block_stats(cfg, kp, vp, seq, rec_p, block_table=table.to(DEV), num_pages=pages)
+    sync()
+    assert torch.equal(rec_c, rec_p)
+    parts = R.decode(rec_p[0, 0].cpu().numpy(), d, r, "f32", "f32", True, True)
+    assert all(np.all(part[2] == 0) and np.all(part[5] == 0) for part in parts[1:])     # means, factors, skew
+    assert np.any(parts[2][1] != 0) and np.any(parts[3][1] != 0) and int(parts[0][2]) == L
+
 # -------------------------------------------------------- block statistics --
 
 def _stats_cache(law, d, nblk, tail, seed, L=64):
