@@ -772,23 +772,44 @@ constexpr size_t select_refresh_lds() {
                  lds_max<wave_stats_lds_bytes<D, kL, true>(), block_mean_lds_bytes<D>()>()>();
 }
 
+// The arguments of a kernel that takes them as one struct, loaded from the kernarg
+// segment here (scalar loads): no values loaded earlier are held in their place.
+template <class Args>
+__device__ __forceinline__ Args load_kernel_args() {
+  typedef const __attribute__((address_space(4))) Args* kernarg_t;
+  kernarg_t a = (kernarg_t)__builtin_amdgcn_kernarg_segment_ptr();
+  __asm__ volatile("" : "+s"(a));
+  return *(const Args*)a;
+}
+
+// What bounds the refresh of a partial block (63 steps of 64): its workgroup's
+// chain of loads, barriers and address arithmetic before it can score.  Where the
+// refresh runs, it loads the arguments for itself, and the scoring after it loads
+// them again: the scalar registers cannot hold them over both, and the compiler
+// kept them in vector lanes, 188 lane reads on the way of a partial block (14 now).
+// The other workgroups go on with the arguments loaded at the start.  Steps with
+// bf16 / E2M1 records, 8 KV heads of 4 heads: 4 rows of 33k to 65k tokens, paged,
+// 36.1 -> 35.2 us, one row of 32k tokens 22.9 -> 22.5; with fp32 records the step is
+// the same to 0.1 %.
 template <int D, int G, int MDT, int FDT>
 __device__ __forceinline__ void select_refresh_task(const SelectParams& p, char* pool) {
   const int b = blockIdx.z, h = blockIdx.y, chunk = blockIdx.x;
+  SelectParams ps = p;
   const int T = clamp_len(p.seq_lens[b], p.tmax);
   if (T > 0 && ((T - 1) / kL) / p.bpw == chunk) {
     const int j = (T - 1) / kL;
+    const SelectParams pr = load_kernel_args<SelectParams>();
     StatsArgs a;
-    a.kv = p.kv;
-    a.rec = p.tail_rec;
-    a.hkv = p.hkv;
-    a.nbmax = p.nbmax;
-    a.r = p.r;
-    a.mdt = p.mdt;
-    a.fdt = p.fdt;
-    a.skew = p.skew;
-    a.vmean = p.vmean;
-    a.lay = p.lay;
+    a.kv = pr.kv;
+    a.rec = pr.tail_rec;
+    a.hkv = pr.hkv;
+    a.nbmax = pr.nbmax;
+    a.r = pr.r;
+    a.mdt = pr.mdt;
+    a.fdt = pr.fdt;
+    a.skew = pr.skew;
+    a.vmean = pr.vmean;
+    a.lay = pr.lay;
     a.basis = nullptr;
     a.fd = D;
     // a full block by one wave (bitwise the build's); a partial one, whose
@@ -798,16 +819,18 @@ __device__ __forceinline__ void select_refresh_task(const SelectParams& p, char*
     else if (threadIdx.x < 64) block_stats_wave<D, kL, false, true>(a, b, h, j, n, pool);
     __builtin_amdgcn_s_waitcnt(0);       // the record is written before it is scored
     __syncthreads();
+    ps = load_kernel_args<SelectParams>();
   }
-  if constexpr (MDT != DT_F32 && FDT != DT_F32) select_mfma_task<D, G, 4, MDT, FDT>(p, b, h, chunk, pool);
-  else select_task<D, G, 4, MDT, FDT>(p, b, h, chunk, pool);
+  if constexpr (MDT != DT_F32 && FDT != DT_F32) select_mfma_task<D, G, 4, MDT, FDT>(ps, b, h, chunk, pool);
+  else select_task<D, G, 4, MDT, FDT>(ps, b, h, chunk, pool);
 }
 
-// Instantiations whose scoring loop fits three workgroups per CU without
-// spills get that cap (the refresh routine's accumulators would otherwise push
-// them to two; with the cap, 22-25 registers of the inlined block statistics
-// go to scratch, outside the scoring loop); the others keep the compiler's
-// choice.
+// Instantiations whose scoring loop fits the 168 registers of three workgroups per
+// CU get that cap.  They then take 128 to 152, none spilled; d = 64, G = 8 with an
+// fp32 half 167 or 168, up to five spilled.  Left to itself the compiler takes 176 to
+// 216 for them, two workgroups per CU.  The others would spill under the cap (bf16 /
+// bf16 at d = 128 109 registers, fp32 with G = 8 83, G = 16 at d = 64 172) and keep
+// the compiler's choice, 216 to 470 registers.
 template <int D, int G, int MDT, int FDT>
 constexpr bool select_refresh_capped() {
   if (MDT != DT_F32 && FDT != DT_F32) return !(D == 128 && FDT == DT_BF16);
