@@ -33,11 +33,13 @@
 //     permuted.  The factor pass forms Kc^T w / sqrt(n) as above, then
 //     xi_ss = U^T xi, on which the sign rule and the record work.
 //
-// What bounds it: instruction issue.  A block takes 13.6k vector and 1.4k matrix
-// instructions (62k and 40k cycles of a SIMD), which at twelve waves per CU fill
-// the SIMDs: 1,364 us for 32,768 blocks (d = 128, L = 64, r = 4, bf16 keys).  With
-// twice the registers (eight waves), broadcasts as moves of their own in the
-// Cholesky, all Gram tiles and sixteen-lane fp64 column sums it took 1,817.
+// What bounds it: the chain of dependent instructions within a wave, at eleven
+// waves per CU (see WaveStatsLds).  A block (d = 128, L = 64, r = 4, bf16 keys) takes
+// 15.0k vector and 1.4k matrix instructions, 61k and 40k cycles of a SIMD's two
+// pipes.  32,768 blocks take 1,362 us, in which the counters show the vector pipes
+// active for 63 % and the matrix pipes for 41 % of the time: they hardly overlap.
+// With twice the registers (eight waves), broadcasts as moves of their own in the
+// Cholesky, all Gram tiles and sixteen-lane fp64 column sums it took 1,817 us.
 #pragma once
 
 #include "block_stats.h"
@@ -88,7 +90,9 @@ __device__ __forceinline__ void write_record_wave(const StatsArgs& p, uint8_t* R
 // product of the power iteration.  The means take the first bytes while the
 // Gram matrix is formed (then registers), the Gram tiles being transposed the
 // same ones; the Rayleigh-Ritz, Jacobi and factor buffers, written after the last
-// product, take Gamma's.  At L = 64, d = 128 this is 13,632 bytes: twelve waves per CU.
+// product, take Gamma's.  At L = 64 this is 13,632 bytes, 14,080 in the units of 1,280
+// bytes that LDS is allotted in: eleven one-wave workgroups per CU, measured (twelve
+// run together with 12,800 bytes and no more); 10,240 bytes at most at L = 32: sixteen.
 template <int D, int LB>
 struct WaveStatsLds {
   static constexpr int P = 16, PS = P + 1;
@@ -152,8 +156,8 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
   constexpr int NT16 = LB / 16;                 // 16-row tiles of the block
   constexpr int CPL = D / 4;                    // columns of a lane group
   constexpr int NCH = CPL / 8;                  // 8-column chunks of a lane group
-  constexpr int EPL = D / 64;                   // columns of a lane (skew)
-  constexpr int FPR = D / 16;                   // features of a lane in the projection Z
+  constexpr int EPL = D / 64;                   // columns of a lane in the factor pass
+  constexpr int FPR = D / 16;                   // columns of a lane in the column means
   float* mean = reinterpret_cast<float*>(pool + Lay::mean);
   float* vmean = reinterpret_cast<float*>(pool + Lay::vmean);
   float* Yp = reinterpret_cast<float*>(pool + Lay::yp);
@@ -251,9 +255,9 @@ __device__ __forceinline__ void block_stats_wave(const StatsArgs& p, int b, int 
   auto feature = [&](const uint32_t* w, int e) -> float {
     return KF32 ? __uint_as_float(w[KF32 ? e : 0]) : (e % 2 ? bf16_hi(w[e / 2]) : bf16_lo(w[e / 2]));
   };
-  // column means into LDS: fp64 sums (exact for the block's fp32 values unless
-  // their magnitudes span > 2^29), one rounding to fp32, so a block of
-  // identical rows centres to exact zeros.  A lane adds its rows; the four lane
+  // column means, FPR of them in each lane: fp64 sums (exact for the block's fp32
+  // values unless their magnitudes span > 2^29), one rounding to fp32, so a block
+  // of identical rows centres to exact zeros.  A lane adds its rows; the four lane
   // groups' sums meet by lane swaps.
   const bool whole = n == LB && kbase >= 0;
   constexpr int QB = (KF32 && NT16 > 2) ? NT16 / 2 : NT16;     // row tiles in flight together

@@ -16,9 +16,9 @@ constexpr int kWgColumns = 32;           // power-iteration columns of the four-
 // Workgroups per CU (waves per SIMD) that the registers are fitted to, by the
 // LDS that a block takes.  A block's serial parts (Cholesky on one wave, Jacobi's
 // rounds) leave the CU to the others: 2,048 blocks of 128 tokens (d = 128,
-// r = 4, bf16 keys) take 1,320 us with four (128 registers, 192 spilled, mostly
-// the Gram matrix across the Cholesky), 1,436 with three, and took 3,534 with
-// one, which 107 KB of LDS allowed.
+// r = 4, bf16 keys) take 1,350 us with four (128 registers, 200 spilled, mostly
+// the Gram matrix across the Cholesky) and 1,461 with three (43 spilled); they
+// took 3,534 with one, which 107 KB of LDS allowed.
 template <int D, int LB, bool KF32, bool SS>
 constexpr int wg_build_waves() {
   if (SS) return 1;
@@ -61,11 +61,11 @@ __global__ __launch_bounds__(kBuildThreads, WAVES) void build_stats_kernel(Build
 template <size_t A, size_t B>
 constexpr size_t size_max() { return A > B ? A : B; }
 
-// Waves per SIMD that the registers are fitted to: the routine is bound by
-// issue and by the latencies of its serial parts, so more blocks in flight pay
-// up to what LDS holds (twelve waves per CU at L = 64, sixteen at L = 32);
-// subspace factors of fp32 keys hold too many projected keys for three.  The
-// step's single newest block (NT = 256) has the SIMD to itself.
+// Waves per SIMD that the registers are fitted to: the routine is bound by the
+// latencies of its serial parts, so more blocks in flight pay up to what LDS holds
+// (eleven waves per CU at L = 64, sixteen at L = 32); subspace factors of fp32 keys
+// hold too many projected keys for three.  The step's single newest block
+// (NT = 256) has the SIMD to itself.
 template <int D, int LB, bool KF32, int FD, int NT>
 constexpr int wave_build_waves() {
   if (NT > 64) return 2;
@@ -146,8 +146,9 @@ hipError_t launch_build_wave(const BuildParams& p, dim3 grid, hipStream_t st) {
 }
 
 // With no more blocks than the device has CUs each workgroup has a CU to itself,
-// and nothing is gained by fewer registers: the decode step's build of four newest
-// blocks of 128 tokens costs the step 5 us more on the four-to-a-CU form.
+// and nothing is gained by fewer registers: a decode step over four units with
+// blocks of 128 tokens takes 35.4 us on the four-to-a-CU form, 30.3 on this one (387
+// and 356 when it fills the blocks).
 template <int D, int LB, bool KF32, bool SS>
 void launch_build_wg_as(const BuildParams& p, dim3 grid, hipStream_t st) {
   if ((int64_t)grid.x * grid.y * grid.z <= device_cus())
