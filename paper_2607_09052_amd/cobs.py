@@ -10,7 +10,6 @@ there is no other implementation to fall back to.
 import ctypes
 import dataclasses
 import math
-import operator
 import os
 
 import torch
@@ -110,25 +109,31 @@ class Config(_CForm):
     # U_Q of every KV head for subspace factors: fp32 [Hkv, d, subspace_dim] on the GPU
     query_basis: object = dataclasses.field(default=None, compare=False, repr=False)
 
+    def __setattr__(self, name, value):
+        object.__setattr__(self, name, value)
+        object.__setattr__(self, "_c_form", None)      # after the field: see marshalled
+
     def __getstate__(self):
         return self.__dict__
 
     def marshalled(self):
         """The C form of the fields: (struct, record bytes, K/V torch dtype or None).
-        It is kept with the values that it was made from and used again while every
-        field is the same object, however it may have been set.  Only plain numbers
-        and texts are compared so: with anything that can change in place (a query
-        basis, an array) it is made anew for each call."""
+        It is kept with a copy of the fields that it was made from, until a field is
+        assigned, and used while they are equal: a field may also be set past
+        __setattr__ (vars(), a new __dict__).  Only plain numbers and texts are
+        kept: with anything that can change in place (a query basis, an array) the
+        form is made anew for each call."""
         kept = getattr(self, "_c_form", None)
-        fields = _config_fields(self)
-        if kept is not None and all(map(operator.is_, fields, kept[0])):
+        if kept is not None and self.__dict__ == kept[0]:
             return kept[1]
-        plain = type(self) is Config and fields[-1] is None and all(type(x) in _PLAIN for x in fields[:-1])
-        src = Config(*fields) if plain else self       # the values read, if another thread sets one meanwhile
+        fields = dict(self.__dict__)
+        plain = (type(self) is Config and fields.keys() == _FIELDS and fields["query_basis"] is None and
+                 all(type(x) in _PLAIN for x in fields.values()))
+        src = Config(**fields) if plain else self      # the values read, if another thread sets one meanwhile
         c = src.c_struct()
         form = (c, int(lib().cobs_record_bytes(ctypes.byref(c))), _TORCH_DTYPE.get(src.kv_dtype))
         if plain:
-            self._c_form = (fields, form)
+            object.__setattr__(self, "_c_form", (fields, form))
         return form
 
     @property
@@ -157,8 +162,8 @@ class Config(_CForm):
         return self.softmax_scale if self.softmax_scale > 0 else 1.0 / math.sqrt(self.head_dim)
 
 
-_config_fields = operator.attrgetter(*(f.name for f in dataclasses.fields(Config)))    # query_basis is the last
-_PLAIN = (int, float, bool, str)
+_FIELDS = {f.name for f in dataclasses.fields(Config)}
+_PLAIN = (int, float, bool, str, type(None))
 
 
 def _ptr(t):
