@@ -111,6 +111,8 @@ __global__ __launch_bounds__(kCmpThreads) void compress_kernel(CompressParams p)
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const bool live = whole() || base + 4 * u + grp < nb;
+      // an infinite scale times its zero codes is NaN, and so is the score
+      const float s = (MDT == DT_E2M1) ? __builtin_fmaf(ks[u], 0.0f, ks[u]) : 1.0f;
       float x[EPL];
       unpack_elems<MDT, EPL>(kw[u], x);
 #pragma unroll
@@ -118,7 +120,7 @@ __global__ __launch_bounds__(kCmpThreads) void compress_kernel(CompressParams p)
         float a = 0.0f;
 #pragma unroll
         for (int e = 0; e < EPL; ++e) a += x[e] * q[g][e];
-        a = row16_sum(a) * ks[u];
+        a = row16_sum(a) * s;
         sc[u][g] = live ? a : -INFINITY;
       }
     }

@@ -286,3 +286,28 @@ def test_compression_branch_with_infinite_values(d, G, md, B, Hkv):
                 assert fin.sum() == d - 2 and rel_l2(got[i][fin], o[i][fin]) <= 1e-5, (b, h, i)
             np.testing.assert_allclose(lse[b, gs].cpu().numpy(), l, rtol=0,
                                        atol=LSE_TOL * max(1.0, float(np.max(np.abs(l)))))
+
+
+@pytest.mark.parametrize("d,md,bad", [(128, "f32", float("nan")), (64, "bf16", float("nan")),
+                                      (128, "e2m1", float("inf")), (64, "e2m1", float("inf"))])
+def test_compression_branch_with_a_score_that_is_no_number(d, md, bad):
+    """A block whose stored mean key has no finite score (an element that is NaN,
+    or the zero codes of an infinite E2M1 scale): every head of the row returns
+    zeros and a log-sum of -inf; rows without such a block are not touched."""
+    B, Hkv, G, L, nb = 2, 2, 4, 32, 21
+    g = torch.Generator(device=DEV)
+    g.manual_seed(900 + d)
+    k, v = (torch.randn(B, Hkv, nb * L, d, generator=g, device=DEV).to(torch.bfloat16) for _ in range(2))
+    q = torch.randn(B, G * Hkv, d, generator=g, device=DEV)
+    k[0, :, 5 * L + 3, 7] = bad
+    cfg = _cfg(d, 0, "bf16", md, "bf16", nb * L, G=G, B=B, Hkv=Hkv, value_mean=True, block_size=L)
+    seq = torch.full((B,), nb * L, dtype=torch.int32, device=DEV)
+    rec = cobs.new_summaries(cfg, DEV)
+    say(f"compression branch with a score that is no number d={d} mean {md}")
+    cobs.cobs_build_block_stats(cfg, k, v, seq, rec)
+    out = torch.full((B, G * Hkv, d), 7.0, dtype=torch.float32, device=DEV)
+    lse = torch.full((B, G * Hkv), 7.0, dtype=torch.float32, device=DEV)
+    cobs.cobs_compression_branch(cfg, q, rec, seq, out, lse)
+    sync()
+    assert torch.all(out[0] == 0) and torch.all(torch.isneginf(lse[0]))
+    assert torch.all(torch.isfinite(out[1])) and torch.all(torch.isfinite(lse[1]))
